@@ -144,13 +144,13 @@ __device__ __forceinline__ void rev_load(RevFrags<T, DK, GATE, C>& f, const BwdA
   const FwdArgs& a = ba.f;
   const int64_t t0 = static_cast<int64_t>(i) * C;
   const int last = static_cast<int>(min<int64_t>(C, a.T - t0)) - 1;
-  const int64_t cc = (x.bh * a.NT + i) * (int64_t)(C * C);
-  const int64_t ck = (x.bh * a.NT + i) * (int64_t)(DK * C);
+  const int64_t cc = a.ci(x.bh, i) * (int64_t)(C * C);
+  const int64_t ck = a.ci(x.bh, i) * (int64_t)(DK * C);
   const T* pt = static_cast<const T*>(a.PtT) + cc;
   const T* mt = static_cast<const T*>(a.MtT) + cc;
   // decayed write-key rows w_r Kt: stored for the per-channel gate; with a
   // scalar gate (or none) the plain rows, w_r applied to the product's rows
-  const T* kw = static_cast<const T*>(GATE == kGateChannel ? a.Kw : a.Ktr) + (x.bh * a.Tpad + t0) * DK;
+  const T* kw = static_cast<const T*>(GATE == kGateChannel ? a.Kw : a.Ktr) + a.ci(x.bh, i) * (C * DK);
   const T* ql = static_cast<const T*>(a.QlT) + ck;
   const T* kn = static_cast<const T*>(a.KnT) + ck;
   const int ra = 16 * x.w + x.lr;
@@ -182,7 +182,7 @@ __device__ __forceinline__ void rev_load(RevFrags<T, DK, GATE, C>& f, const BwdA
     for (int ii = 0; ii < 4; ++ii) f.gw[ii] = rows ? a.G[x.bh * a.Tpad + t0 + 16 * x.w + 4 * x.lg + ii] : 0.f;
   }
   if (GATE == kGateChannel) {
-    const float* gl = a.G + (x.bh * a.NT + i) * DK;   // G at the chunk end
+    const float* gl = a.G + a.ci(x.bh, i) * DK;   // G at the chunk end
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
@@ -241,7 +241,7 @@ __device__ __forceinline__ void rev_step(RevFrags<T, DK, GATE, C>& f, bool stage
   // state adjoint entering this chunk from the right, rows c, slab columns
   // (its LDS reads after the operand reads: LDS reads complete in issue order)
   if (WR)
-    slab_to_rows<DK, true>(static_cast<T*>(ba.dHs) + (x.bh * a.NT + i) * (int64_t)DK * a.dv + x.v0, a.dv,
+    slab_to_rows<DK, true>(static_cast<T*>(ba.dHs) + a.ci(x.bh, i) * (int64_t)DK * a.dv + x.v0, a.dv,
                            sH, LDH, DK, x.tid);
   if (rows) {
 #pragma unroll
@@ -282,7 +282,7 @@ __device__ __forceinline__ void rev_step(RevFrags<T, DK, GATE, C>& f, bool stage
     for (int k2 = 0; k2 < KC; ++k2) bX[vt][k2] = ld8(swc<C>(sX, LDE, 16 * vt + lr, k2 * 32 + 8 * lg));
   if (WR) {
     // Z and dv rows (their LDS reads after the operand reads)
-    const int64_t r0 = (x.bh * a.Tpad + t0) * a.dv + x.v0;
+    const int64_t r0 = a.ci(x.bh, i) * (C * static_cast<int64_t>(a.dv)) + x.v0;
     slab_to_rows<C, true>(static_cast<T*>(ba.Zr) + r0, a.dv, sZ, LDE, C, x.tid);
     const int64_t HV = a.H * (int64_t)a.dv;
     slab_to_rows<C, FULL>(static_cast<T*>(ba.dv) + (x.b * a.T + t0) * HV + x.h * a.dv + x.v0, HV, sX, LDE,
@@ -710,8 +710,8 @@ __global__ __launch_bounds__(256, 2) void p12_chunk_grads(BwdArgs ba) {
   const int64_t t0 = static_cast<int64_t>(i) * C;
   const int n = static_cast<int>(min<int64_t>(C, a.T - t0));
   const int64_t HV = a.H * (int64_t)DV, HD = a.H * (int64_t)DK;
-  const int64_t rv = (bh * a.Tpad + t0) * DV, rk = (bh * a.Tpad + t0) * DK;
-  const int64_t cs = (bh * a.NT + i) * (int64_t)DK * DV;
+  const int64_t rv = a.ci(bh, i) * (C * DV), rk = a.ci(bh, i) * (C * DK);
+  const int64_t cs = a.ci(bh, i) * (int64_t)DK * DV;
 
   // ---- A operands of row ra (wave-private)
   const int ra = 16 * w + lr;
@@ -1097,8 +1097,8 @@ __global__ __launch_bounds__(256, 2) void p12c_chunk_grads(BwdArgs ba) {
   const int64_t t0 = static_cast<int64_t>(i) * C;
   const int n = static_cast<int>(min<int64_t>(C, a.T - t0));
   const int64_t HV = a.H * (int64_t)DV, HD = a.H * (int64_t)DK;
-  const int64_t rv = (bh * a.Tpad + t0) * DV, rk = (bh * a.Tpad + t0) * DK;
-  const int64_t cs = (bh * a.NT + i) * (int64_t)DK * DV;
+  const int64_t rv = a.ci(bh, i) * (C * DV), rk = a.ci(bh, i) * (C * DK);
+  const int64_t cs = a.ci(bh, i) * (int64_t)DK * DV;
 
   const int ra = 16 * w + lr;
   const uint32_t rc = static_cast<uint32_t>(min(ra, n - 1));
@@ -1566,8 +1566,8 @@ __global__ __launch_bounds__(64 * (C / PCG)) void pc_chunk(BwdArgs ba) {
   constexpr uint32_t E = sizeof(T);
   const uint32_t kstb = static_cast<uint32_t>(a.H * DK) * E, lo = static_cast<uint32_t>(c0) * E;
   const T* kb = static_cast<const T*>(a.k) + ((b * a.T + t0) * a.H + h) * DK;
-  const T* gb = static_cast<const T*>(ba.dKt) + (bh * a.Tpad + t0) * DK;
-  const T* mb = static_cast<const T*>(ba.dKm) + (bh * a.Tpad + t0) * DK;
+  const T* gb = static_cast<const T*>(ba.dKt) + a.ci(bh, i) * (C * DK);
+  const T* mb = static_cast<const T*>(ba.dKm) + a.ci(bh, i) * (C * DK);
   // per-segment values of this chunk: [BH, NT, PCS, DK]
   const int64_t segb = ((bh * a.NT + i) * PCS) * DK;
   // the per-token inputs first (lane = token; every wave loads them, so no
@@ -1845,7 +1845,7 @@ __global__ __launch_bounds__(256) void combine_dk(BwdArgs ba) {
   const int c = static_cast<int>(idx % DK);
   const int64_t tok = idx / DK;
   const int64_t h = tok % a.H, t = (tok / a.H) % a.T, b = tok / (a.H * a.T);
-  const int64_t w = ((b * a.H + h) * a.Tpad + t) * DK + c;
+  const int64_t w = (a.ci(b * a.H + h, t / a.chunk) * a.chunk + t % a.chunk) * DK + c;
   const float km = to_f(static_cast<const T*>(ba.dKm)[w]), kt = to_f(static_cast<const T*>(ba.dKt)[w]);
   if (a.precond == kIdentity) {
     static_cast<T*>(ba.dk)[idx] = from_f<T>(km + kt);
@@ -1867,12 +1867,19 @@ BwdWsLayout bwd_ws_layout(int64_t BH, int NT, int dk, int dv, int esz, int gate,
   const size_t bh = static_cast<size_t>(BH), nt = static_cast<size_t>(NT), tp = nt * C;
   L.Hs = take(bh * nt * dk * dv * esz);
   L.Er = take(bh * tp * dv * esz);
-  L.PtT = take(bh * nt * C * C * esz);
-  L.MtT = take(bh * nt * C * C * esz);
-  L.Ktr = take(bh * tp * dk * esz);
-  L.Kw = gate == kGateChannel ? take(bh * tp * dk * esz) : 0;   // = w_r Kt rows, per-channel gate only
-  L.QlT = take(bh * nt * dk * C * esz);
-  L.KnT = take(bh * nt * dk * C * esz);
+  if (esz == 4) {
+    L.PtT = take(bh * nt * C * C * esz);
+    L.MtT = take(bh * nt * C * C * esz);
+  }
+  // bf16: the forward's write-key rows (Kd) serve as the plain rows, or with
+  // the per-channel gate as the decayed ones
+  const bool rows = esz == 2, chan = gate == kGateChannel;
+  L.Ktr = rows && !chan ? L.f.KtG : take(bh * tp * dk * esz);
+  L.Kw = !chan ? 0 : rows ? L.f.KtG : take(bh * tp * dk * esz);
+  if (!rows) {
+    L.QlT = take(bh * nt * dk * C * esz);
+    L.KnT = take(bh * nt * dk * C * esz);
+  }
   L.dHs = take(bh * nt * dk * dv * esz);
   L.Zr = take(bh * tp * dv * esz);
   L.dKt = take(bh * tp * dk * esz);
@@ -1897,7 +1904,9 @@ static hipError_t launch_bwd_typed(const BwdArgs& ba, hipStream_t s, hipEvent_t 
   const int nslab = DV / BVB, npslab = DK / BVB;
   auto grid_scan = [&](int nrole) { return dim3(static_cast<unsigned>(((a.BH + 7) / 8) * 8 * nrole)); };
   const unsigned grid_chunk = static_cast<unsigned>(a.BH * a.NT);
-  if (a.seg_cnt < 3) {
+  if constexpr (sizeof(T) == 2) {
+    if ((e = launch_rev_scan_bf16(ba, s)) != hipSuccess) return e;
+  } else if (a.seg_cnt < 3) {
     BwdArgs b0 = ba;
     b0.f.seg_phase = 0;
     hipLaunchKernelGGL((r1_state_adjoint<T, DK, GATE, C>), grid_scan(nslab), dim3(256), 0, s, b0);

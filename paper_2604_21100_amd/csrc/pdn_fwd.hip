@@ -193,6 +193,10 @@ __global__ __launch_bounds__(256, 3) void k2_chunk_prep(FwdArgs a) {
   constexpr int NB = C / 16;
   static_assert(NB == 2 || NB == 4, "chunk of 32 or 64 tokens");
   constexpr bool NOQ = SM::NOQ;
+  // bf16: the scan reads M and write-key rows (it scales E by beta and w and
+  // reads the rows transposed from LDS); fp32: T and the transposed decayed
+  // write keys
+  constexpr bool ROWS = sizeof(T) == 2;
   constexpr int LDK = SM::LDK, LDA = SM::LDA;
   __shared__ __attribute__((aligned(16))) char smem[SM::kTotal];
   T* sK = reinterpret_cast<T*>(smem);
@@ -350,7 +354,7 @@ __global__ __launch_bounds__(256, 3) void k2_chunk_prep(FwdArgs a) {
         *gp = x;
       }
     }
-    if (sg == NSG - 1) a.G[(bh * a.NT + i) * DK + c] = x;   // row C - 1
+    if (sg == NSG - 1) a.G[a.ci(bh, i) * DK + c] = ROWS ? fast_exp(x) : x;   // row C - 1
   }
   if (has_gram(PREC)) {
     // the in-chunk prefix A_r = a_r A_{r-1} + bP_r k_r^2 in NSEG row segments:
@@ -479,7 +483,7 @@ __global__ __launch_bounds__(256, 3) void k2_chunk_prep(FwdArgs a) {
   __syncthreads();
   if (PREC == kATQ) {
     // the preconditioned query rows for the scan's inter-chunk output
-    T* qt = static_cast<T*>(a.Qt) + (bh * a.Tpad + t0) * DK;
+    T* qt = static_cast<T*>(a.Qt) + a.ci(bh, i) * (C * DK);
     static_assert((C * VPR) % 256 == 0, "whole rounds of 256 threads");
 #pragma unroll
     for (int jj = 0; jj < (C * VPR) / 256; ++jj) {
@@ -504,8 +508,8 @@ __global__ __launch_bounds__(256, 3) void k2_chunk_prep(FwdArgs a) {
     // backward their transposes (Lam o Q)^T and -(Lam o K)^T, [dk][C].  A
     // thread takes 8 rows x 4 channels, so each exponential serves all four
     // outputs.
-    T* ql = static_cast<T*>(a.QL) + (bh * a.Tpad + t0) * DK;
-    T* kl = static_cast<T*>(a.KL) + (bh * a.Tpad + t0) * DK;
+    T* ql = static_cast<T*>(a.QL) + a.ci(bh, i) * (C * DK);
+    T* kl = static_cast<T*>(a.KL) + a.ci(bh, i) * (C * DK);
     const T* qg = static_cast<const T*>(a.q) + ((b * a.T + t0) * a.H + h) * DK;
     using V4 = typename Vec4<T>::type;
     constexpr int RB = C / 8, NTILE = RB * (DK / 4);
@@ -541,9 +545,9 @@ __global__ __launch_bounds__(256, 3) void k2_chunk_prep(FwdArgs a) {
         st4<T>(ql + r * DK + c0, qo[0], qo[1], qo[2], qo[3]);
         st4<T>(kl + r * DK + c0, ko[0], ko[1], ko[2], ko[3]);
       }
-      if (BWD) {
-        T* QlT = static_cast<T*>(a.QlT) + (bh * a.NT + i) * (int64_t)(DK * C);
-        T* KnT = static_cast<T*>(a.KnT) + (bh * a.NT + i) * (int64_t)(DK * C);
+      if (BWD && !ROWS) {
+        T* QlT = static_cast<T*>(a.QlT) + a.ci(bh, i) * (int64_t)(DK * C);
+        T* KnT = static_cast<T*>(a.KnT) + a.ci(bh, i) * (int64_t)(DK * C);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           st8(QlT + (c0 + e) * C + r0, fq[e]);
@@ -614,7 +618,7 @@ __global__ __launch_bounds__(256, 3) void k2_chunk_prep(FwdArgs a) {
   }
   // masks, beta and scalar decay; P goes straight to the workspace
   if (NB == 4 || w < NB) {
-    T* P = static_cast<T*>(a.Pm) + (bh * a.NT + i) * (int64_t)(C * C);
+    T* P = static_cast<T*>(a.Pm) + a.ci(bh, i) * (int64_t)(C * C);
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
       const int t = 16 * j + lr;
@@ -627,17 +631,17 @@ __global__ __launch_bounds__(256, 3) void k2_chunk_prep(FwdArgs a) {
         accA[j][ii] = (j <= w && r > t) ? sBeta[r] * accA[j][ii] * fac : 0.f;
         P[r * C + t] = from_f<T>(accP[j][ii]);
       }
-      if (BWD) {
-        T* PtT = static_cast<T*>(a.PtT) + (bh * a.NT + i) * (int64_t)(C * C);
+      if (BWD && !ROWS) {
+        T* PtT = static_cast<T*>(a.PtT) + a.ci(bh, i) * (int64_t)(C * C);
         st_tile_t<T>(PtT + (16 * j) * C + 16 * w, C, accP[j], lr, lg);
       }
     }
   }
-  if (BWD && GATE != kGateChannel) {
+  if (BWD && !ROWS && GATE != kGateChannel) {
     // (Lam o Q)^T and -(Lam o K)^T per chunk, [dk][C] (per-channel gate:
     // written with the Lam o Q / Lam o K rows above)
-    T* QlT = static_cast<T*>(a.QlT) + (bh * a.NT + i) * (int64_t)(DK * C);
-    T* KnT = static_cast<T*>(a.KnT) + (bh * a.NT + i) * (int64_t)(DK * C);
+    T* QlT = static_cast<T*>(a.QlT) + a.ci(bh, i) * (int64_t)(DK * C);
+    T* KnT = static_cast<T*>(a.KnT) + a.ci(bh, i) * (int64_t)(DK * C);
     static_assert((DK * (C / 8)) % 256 == 0, "whole rounds of 256 threads");
 #pragma unroll
     for (int jj = 0; jj < (DK * (C / 8)) / 256; ++jj) {
@@ -657,11 +661,10 @@ __global__ __launch_bounds__(256, 3) void k2_chunk_prep(FwdArgs a) {
   }
   // the write-key outputs (they need only sKt and the gate prefix), before
   // the solve
-  if (BWD) {
+  if (BWD || (ROWS && GATE != kGateChannel)) {
     // write-key rows (the per-channel gate's decayed rows w_r o Kt go out
-    // with the transposed decayed write keys below; with a scalar gate the
-    // reverse scan applies w_r itself)
-    T* Kr = static_cast<T*>(a.Ktr) + (bh * a.Tpad + t0) * DK;
+    // below; with a scalar gate the scans apply w_r themselves)
+    T* Kr = static_cast<T*>(ROWS && GATE != kGateChannel ? a.Kd : a.Ktr) + a.ci(bh, i) * (C * DK);
     static_assert((C * (DK / 8)) % 256 == 0, "whole rounds of 256 threads");
 #pragma unroll
     for (int jj = 0; jj < (C * (DK / 8)) / 256; ++jj) {
@@ -670,13 +673,14 @@ __global__ __launch_bounds__(256, 3) void k2_chunk_prep(FwdArgs a) {
       st8(Kr + r * DK + c0, ld8(k2sw(sKt, LDK, r, c0)));
     }
   }
-  // ---- decayed write keys, transposed per chunk: (Kt * Lam_C / Lam_t)^T
+  // ---- decayed write keys: rows (bf16, per-channel gate), transposed per
+  // chunk (fp32: (Kt * Lam_C / Lam_t)^T)
   if (GATE == kGateChannel) {
     // w_t = exp(G_{C-1} - G_t) per channel, 8 rows x 4 channels a thread:
     // each factor serves the transposed tile for the scan and, for the
     // backward, the row-major w o Kt
-    T* Kout = static_cast<T*>(a.KtG) + (bh * a.NT + i) * (int64_t)(DK * C);
-    T* Kw = static_cast<T*>(a.Kw) + (bh * a.Tpad + t0) * DK;
+    T* Kout = static_cast<T*>(a.KtG) + a.ci(bh, i) * (int64_t)(DK * C);
+    T* Kw = static_cast<T*>(ROWS ? a.Kd : a.Kw) + a.ci(bh, i) * (C * DK);
     using V4 = typename Vec4<T>::type;
     constexpr int RB = C / 8, NTILE = RB * (DK / 4);
 #pragma unroll
@@ -699,13 +703,14 @@ __global__ __launch_bounds__(256, 3) void k2_chunk_prep(FwdArgs a) {
           wv[e] = fast_exp(gend[e] - gv[e]) * to_f(kt4[e]);
           f[e].set(s2, wv[e]);
         }
-        if (BWD) st4<T>(Kw + t * DK + c0, wv[0], wv[1], wv[2], wv[3]);
+        if (BWD || ROWS) st4<T>(Kw + t * DK + c0, wv[0], wv[1], wv[2], wv[3]);
       }
+      if (!ROWS)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) st8(Kout + (c0 + e) * C + r0, f[e]);
+        for (int e = 0; e < 4; ++e) st8(Kout + (c0 + e) * C + r0, f[e]);
     }
-  } else {
-    T* Kout = static_cast<T*>(a.KtG) + (bh * a.NT + i) * (int64_t)(DK * C);
+  } else if (!ROWS) {
+    T* Kout = static_cast<T*>(a.KtG) + a.ci(bh, i) * (int64_t)(DK * C);
     static_assert((DK * C / 8) % 256 == 0, "whole rounds of 256 threads");
 #pragma unroll
     for (int jj = 0; jj < (DK * C / 8) / 256; ++jj) {
@@ -777,27 +782,37 @@ __global__ __launch_bounds__(256, 3) void k2_chunk_prep(FwdArgs a) {
     __syncthreads();
   }
 
-  // ---- T = X Diag(beta) (block-lower; upper blocks are zero)
+  // ---- T = X Diag(beta), or in bf16 M = X (block-lower; upper blocks are zero)
   {
-    T* Tout = static_cast<T*>(a.Tm) + (bh * a.NT + i) * (int64_t)(C * C);
+    T* Tout = static_cast<T*>(a.Tm) + a.ci(bh, i) * (int64_t)(C * C);
     constexpr int NV = C * C / 8;
 #pragma unroll
     for (int jj = 0; jj < (NV + 255) / 256; ++jj) {
       const int idx = tid + 256 * jj;
       if (NV % 256 != 0 && idx >= NV) break;
       const int r = idx / (C / 8), t0v = (idx % (C / 8)) * 8;
+      if (ROWS && r < C / 2 && t0v >= C / 2) {
+        // the block right of the diagonal is zero: it carries the chunk's
+        // per-row scalars (lam, w, beta), which reach the scan with M's tile
+        const int q = r * (C / 16) + (t0v - C / 2) / 8, v = q / (C / 4), t4 = 4 * (q % (C / 4));
+        float4 f4 = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (v == 2) f4 = *reinterpret_cast<const float4*>(sBeta + t4);
+        else if (v < 2 && GATE == kGateScalar) f4 = *reinterpret_cast<const float4*>((v == 0 ? sLam : sWt) + t4);
+        *reinterpret_cast<float4*>(Tout + r * C + t0v) = f4;
+        continue;
+      }
       Frag8<T> f;
 #pragma unroll
       for (int s = 0; s < 8; ++s) {
         const int t = t0v + s;
         const bool lower = (t >> 4) < (r >> 4) || ((t >> 4) == (r >> 4) && t <= r);
-        f.set(s, lower ? *k2swc(sX, LDA, r, t) * sBeta[t] : 0.f);
+        f.set(s, lower ? *k2swc(sX, LDA, r, t) * (ROWS ? 1.f : sBeta[t]) : 0.f);
       }
       st8(Tout + r * C + t0v, f);
     }
   }
-  if (BWD) {
-    const int64_t cc = (bh * a.NT + i) * (int64_t)(C * C);
+  if (BWD && !ROWS) {
+    const int64_t cc = a.ci(bh, i) * (int64_t)(C * C);
     T* MtT = static_cast<T*>(a.MtT) + cc;
     constexpr int NV = C * C / 8;
 #pragma unroll
@@ -897,14 +912,14 @@ __device__ __forceinline__ void scan_load(ScanFrags<T, DK, GATE, C>& f, const Fw
   // in the workspace (row stride d_k)
   constexpr bool CH = GATE == kGateChannel;
   const int64_t ldk = CH ? DK : HD;
-  const T* kb = CH ? static_cast<const T*>(a.KL) + (x.bh * a.Tpad + t0) * DK
+  const T* kb = CH ? static_cast<const T*>(a.KL) + a.ci(x.bh, i) * (C * DK)
                    : static_cast<const T*>(a.k) + (x.b * a.T + t0) * HD + x.h * DK;
-  const T* qb = CH ? static_cast<const T*>(a.QL) + (x.bh * a.Tpad + t0) * DK
+  const T* qb = CH ? static_cast<const T*>(a.QL) + a.ci(x.bh, i) * (C * DK)
                    : static_cast<const T*>(a.q) + (x.b * a.T + t0) * HD + x.h * DK;
   const T* vb = static_cast<const T*>(a.v) + (x.b * a.T + t0) * HV + x.h * a.dv + x.v0;
-  const T* tb = static_cast<const T*>(a.Tm) + (x.bh * a.NT + i) * (int64_t)(C * C);
-  const T* pb = static_cast<const T*>(a.Pm) + (x.bh * a.NT + i) * (int64_t)(C * C);
-  const T* gb = static_cast<const T*>(a.KtG) + (x.bh * a.NT + i) * (int64_t)(DK * C);
+  const T* tb = static_cast<const T*>(a.Tm) + a.ci(x.bh, i) * (int64_t)(C * C);
+  const T* pb = static_cast<const T*>(a.Pm) + a.ci(x.bh, i) * (int64_t)(C * C);
+  const T* gb = static_cast<const T*>(a.KtG) + a.ci(x.bh, i) * (int64_t)(DK * C);
   // the value slab first: the step before this chunk's stages it into LDS
   // and so waits for it a step earlier than for the other operands; the
   // memory counter completes in issue order, so any load issued before it
@@ -926,7 +941,7 @@ __device__ __forceinline__ void scan_load(ScanFrags<T, DK, GATE, C>& f, const Fw
     // gate values below
   } else if (LA) {
     if (PARTS & 1) {
-      const T* qtb = CH ? qb : static_cast<const T*>(a.Qt) + (x.bh * a.Tpad + t0) * DK;
+      const T* qtb = CH ? qb : static_cast<const T*>(a.Qt) + a.ci(x.bh, i) * (C * DK);
       const uint32_t oqt = (rr * static_cast<uint32_t>(DK) + 8 * x.lg) * E;
 #pragma unroll
       for (int kk = 0; kk < KK; ++kk) f.Q[kk] = ld8(at_bytes(qtb, oqt + kk * 32 * E));
@@ -965,7 +980,7 @@ __device__ __forceinline__ void scan_load(ScanFrags<T, DK, GATE, C>& f, const Fw
     f.gC[0][0] = gs[C - 1];
   }
   if (GATE == kGateChannel) {
-    const float* ge = a.G + (x.bh * a.NT + i) * DK;   // G at the chunk end
+    const float* ge = a.G + a.ci(x.bh, i) * DK;   // G at the chunk end
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
@@ -1078,7 +1093,7 @@ __device__ __forceinline__ void scan_step(ScanFrags<T, DK, GATE, C>& f, const fl
   // complete in issue order)
   if (OUT && i > x.c0) flush_output<true, T, C>(a, i - 1, C, sO, x);   // only full chunks precede this one
   if (SAVE)  // chunk-start state S^T of this chunk, rows c, columns of the slab
-    flush_slab_t<DK>(static_cast<T*>(a.Hs) + (x.bh * a.NT + i) * (int64_t)DK * a.dv + x.v0, a.dv, sH,
+    flush_slab_t<DK>(static_cast<T*>(a.Hs) + a.ci(x.bh, i) * (int64_t)DK * a.dv + x.v0, a.dv, sH,
                      LDH, x.tid);
   floatx4 accX[2], accO[2];
 #pragma unroll
@@ -1136,7 +1151,7 @@ __device__ __forceinline__ void scan_step(ScanFrags<T, DK, GATE, C>& f, const fl
 #pragma unroll
     for (int k2 = 0; k2 < KC; ++k2) fE[vt][k2] = ld8(swv<C>(sE, LDE, 16 * vt + lr, k2 * 32 + 8 * lg));
   if (SAVE) {  // E rows of this chunk (whole chunk: padded rows included)
-    const int64_t r0 = (x.bh * a.Tpad + static_cast<int64_t>(i) * C) * a.dv + x.v0;
+    const int64_t r0 = a.ci(x.bh, i) * (C * static_cast<int64_t>(a.dv)) + x.v0;
     flush_slab_t<C>(static_cast<T*>(a.Er) + r0, a.dv, sE, LDE, x.tid);
   }
   if (OUT && rows) {
@@ -1503,8 +1518,12 @@ static hipError_t launch_k2_prec(const FwdArgs& a, hipStream_t s) {
 // segments 1 .. S - 1 from their exact starts.  The first pass's middle
 // segments also write outputs and saved rows for their chunks from the
 // wrong start; the third pass overwrites every one of them.
+// (bf16: pdn_scan.hip)
 template <typename T, int DK, int GATE, bool SAVE, bool OUT, bool LA, int C>
 static hipError_t launch_k3(const FwdArgs& a0, hipStream_t s) {
+  if constexpr (sizeof(T) == 2) {
+    return launch_fwd_scan_bf16(a0, SAVE, OUT, s);
+  } else {
   FwdArgs a = a0;
   const int nslab = a.dv / BV, npslab = DK / BV;
   auto grid = [&](int nrole) { return dim3(static_cast<unsigned>(((a.BH + 7) / 8) * 8 * nrole)); };
@@ -1523,6 +1542,7 @@ static hipError_t launch_k3(const FwdArgs& a0, hipStream_t s) {
   a.seg_phase = 3;
   hipLaunchKernelGGL((k3_chunk_scan<T, DK, GATE, SAVE, OUT, LA, C>), grid((S - 1) * nslab), dim3(256), 0, s, a);
   return hipGetLastError();
+  }
 }
 
 // SAVE: the training forward (k2 in backward mode, k3 also saving the

@@ -216,7 +216,8 @@ static void set_forward_ws(pdn::FwdArgs& a, const pdn::WsLayout& L, const pdn_pr
     a.sumD = reinterpret_cast<float*>(w + L.sumD);
     a.Abound = reinterpret_cast<float*>(w + L.Abound);
   }
-  a.KtG = w + L.KtG;
+  if (p->io == PDN_BF16) a.Kd = w + L.KtG;
+  else a.KtG = w + L.KtG;
   a.Tm = w + L.Tm;
   a.Pm = w + L.Pm;
   if (p->gate != PDN_GATE_NONE) a.G = reinterpret_cast<float*>(w + L.G);
@@ -230,8 +231,11 @@ static void set_forward_ws(pdn::FwdArgs& a, const pdn::WsLayout& L, const pdn_pr
 }
 
 static void set_residuals(pdn::FwdArgs& f, const pdn::BwdWsLayout& L, char* w) {
-  f.Hs = w + L.Hs; f.Er = w + L.Er; f.PtT = w + L.PtT; f.MtT = w + L.MtT;
-  f.Ktr = w + L.Ktr; f.Kw = L.Kw ? w + L.Kw : nullptr; f.QlT = w + L.QlT; f.KnT = w + L.KnT;
+  f.Hs = w + L.Hs; f.Er = w + L.Er;
+  f.Ktr = w + L.Ktr; f.Kw = f.gate == pdn::kGateChannel ? w + L.Kw : nullptr;
+  if (!f.Kd) {   // fp32
+    f.PtT = w + L.PtT; f.MtT = w + L.MtT; f.QlT = w + L.QlT; f.KnT = w + L.KnT;
+  }
 }
 
 // train: the training forward (also leaves the backward's intermediates in

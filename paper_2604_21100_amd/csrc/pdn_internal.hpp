@@ -54,11 +54,12 @@ struct FwdArgs {
   float* sumL;    // [BH, NT, dk]   in-chunk decayed sum of betaP k^2
   float* sumD;    // [BH, NT]       in-chunk sum of gP (log of the decay)
   float* Abound;  // [BH, NT+1, dk] preconditioner state before each chunk
-  void* KtG;      // [BH, NT, dk, C] (Kt * Gamma)^T per chunk, io dtype
-  void* Tm;       // [BH, NT, C, C]  T = (I + At)^{-1} Diag(beta), io dtype
+  void* KtG;      // fp32: [BH, NT, dk, C] (Kt * Gamma)^T per chunk
+  void* Kd;       // bf16: [BH, Tpad, dk] write-key rows (per-channel gate: w_r o Kt rows)
+  void* Tm;       // [BH, NT, C, C]  fp32: T = M Diag(beta); bf16: M = (I + At)^{-1}
   void* Pm;       // [BH, NT, C, C]  causal (Q*Lam)(Kt/Lam)^T, io dtype
   float* G;       // scalar gate: [BH, Tpad] in-chunk log-decay prefix; per-channel
-                  // gate: [BH, NT, dk], its chunk-end row only
+                  // gate: [BH, NT, dk], its chunk-end row only (bf16: its exponential)
   void* Qt;       // [BH, Tpad, dk] io   ATQ: preconditioned query rows q / (A + ridge)
   void* QL;       // [BH, Tpad, dk] io   per-channel gate: Lam o (the query the scan reads)
   void* KL;       // [BH, Tpad, dk] io   per-channel gate: Lam o K
@@ -66,10 +67,11 @@ struct FwdArgs {
   // adjoint kernels.  lam_r = exp(G_r), w_r = exp(G_{C-1} - G_r).
   void* Hs;       // [BH, NT, dk, dv] io  chunk-start states S^T
   void* Er;       // [BH, Tpad, dv] io    E = T X rows
+  // (fp32 only, the transposed operands its reverse scan reads:)
   void* PtT;      // [BH, NT, C, C] io    P^T
   void* MtT;      // [BH, NT, C, C] io    M^T, M = (I + At)^{-1} (T = M Diag(beta))
-  void* Ktr;      // [BH, Tpad, dk] io    write key rows
-  void* Kw;       // [BH, Tpad, dk] io    w_r o write key rows (per-channel gate; else NULL)
+  void* Ktr;      // [BH, Tpad, dk] io    write key rows (bf16 without the per-channel gate: Kd)
+  void* Kw;       // [BH, Tpad, dk] io    w_r o write key rows (per-channel gate, bf16: Kd; else NULL)
   void* QlT;      // [BH, NT, dk, C] io   (Diag(lam) Q)^T per chunk
   void* KnT;      // [BH, NT, dk, C] io   -(Diag(lam) K)^T per chunk
   // sequence split of the state scan (see scan_split): seg_phase 0 = one
@@ -80,6 +82,8 @@ struct FwdArgs {
   float* seg_end;    // [S, BH, dk, dv] phase-1 end states (segment 0: exact; others: local)
   float* seg_phi;    // [S, BH, dk, dk] segment transitions, S_end^T = Phi S_start^T + local
   float* seg_start;  // [S, BH, dk, dv] exact start states of segments 1 .. S - 1
+  // index of head bh's chunk i in the per-chunk workspace tensors
+  __host__ __device__ int64_t ci(int64_t bh, int64_t i) const { return i * BH + bh; }
 };
 
 // Sequence split of the state scan.  A scan workgroup holds one head's
@@ -142,10 +146,17 @@ struct BwdArgs {
   float* pcMu;    // [BH, NT]             preconditioner: partial d mu
 };
 
+// The reverse state-adjoint scan of bf16 problems (pdn_rscan.hip).
+hipError_t launch_rev_scan_bf16(const BwdArgs& b, hipStream_t s);
+
 // The composition pass of a split scan (seg_compose): the exact segment
 // starts from the first pass's end states and transitions, forward or (rev)
 // for the reverse state-adjoint scan.
 hipError_t launch_seg_compose(const FwdArgs& a, bool rev, hipStream_t s);
+
+// The state scan of bf16 problems (pdn_scan.hip): save leaves the chunk-start
+// states and E rows for the backward, out forms the output.
+hipError_t launch_fwd_scan_bf16(const FwdArgs& a, bool save, bool out, hipStream_t s);
 
 struct WsLayout {
   size_t sumL, sumD, Abound, KtG, Tm, Pm, G, Qt, QL, KL, seg_end, seg_phi, seg_start, total;
