@@ -14,7 +14,7 @@ LIB = os.path.join(HERE, "libpdn.so")
 BUILD_DIR = os.path.join(HERE, "_build")
 
 SOURCES = ["pdn_host.cpp", "pdn_fwd.hip", "pdn_bwd.hip", "pdn_scan.hip",
-           "pdn_rscan.hip"]
+           "pdn_rscan.hip", "pdn_step.hip"]
 
 # Packed-fp32 VALU ops are disabled for all device code (they have produced
 # silent wrong results on this hardware generation); hipcc's host pass warns

@@ -1693,8 +1693,25 @@ hipError_t launch_forward(const FwdArgs& a, int io_bf16, hipStream_t s, hipEvent
                        a, nS, nA);
     return hipGetLastError();
   }
-  return a.chunk == 32 ? launch_chunks<32>(a, io_bf16, s, ev, train)
-                       : launch_chunks<64>(a, io_bf16, s, ev, train);
+  if (a.T > kStepTokens) {
+    return a.chunk == 32 ? launch_chunks<32>(a, io_bf16, s, ev, train)
+                         : launch_chunks<64>(a, io_bf16, s, ev, train);
+  }
+  // A few tokens: the token recurrence.  Training forwards run the chunk
+  // kernels for the rows the backward reads and take their outputs from the
+  // recurrence too, so both forwards return the same values.  (The first
+  // three stage events of an inference call mark empty stages.)
+  hipError_t e = hipSuccess;
+  if (train) {
+    hipEvent_t e3[4] = {ev ? ev[0] : nullptr, ev ? ev[1] : nullptr, ev ? ev[2] : nullptr, nullptr};
+    e = a.chunk == 32 ? launch_chunks<32>(a, io_bf16, s, e3, true) : launch_chunks<64>(a, io_bf16, s, e3, true);
+  } else {
+    for (int i = 0; ev && i < 3 && e == hipSuccess; ++i)
+      if (ev[i]) e = hipEventRecord(ev[i], s);
+  }
+  if (e == hipSuccess) e = launch_step_tokens(a, io_bf16, s);
+  if (e == hipSuccess && ev && ev[3]) e = hipEventRecord(ev[3], s);
+  return e;
 }
 
 }  // namespace pdn
