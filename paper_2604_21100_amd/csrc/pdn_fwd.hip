@@ -152,13 +152,13 @@ __device__ __forceinline__ float* k2swc(float* base, int ld, int row, int col) {
 __device__ __forceinline__ float* k2swf(float* base, int ld, int row, int col) {
   return base + row * ld + (col ^ (((row >> 3) & 7) << 2));
 }
-// NOQ (per-channel gate, query not rewritten): the query tile is not staged
-// (its rows are read from HBM where needed), and the solve's X uses the
-// write-key tile's memory, which is dead once the write-key outputs are out.
-// That keeps the block under 80 KB, two per CU.  (For the other gates the
-// HBM reads of the transposed query cost more than a third block per CU
-// gains.)
-template <typename T, int DK, int GATE, int PREC, int C>
+// PSCAN: the state scan forms P itself (scan_forms_p), so this kernel neither
+// reads the queries nor writes P.
+// NOQ: the query tile is not staged, and the solve's X uses the write-key
+// tile's memory, which is dead once the write-key outputs are out.  With PSCAN
+// a block takes 39 KB, four per CU; with the per-channel gate (its query rows
+// are read from HBM where needed) under 80 KB, two per CU.
+template <typename T, int DK, int GATE, int PREC, int C, bool PSCAN_>
 struct K2Smem {
   static constexpr int LDK = DK;              // row (elements; swizzled, unpadded)
   static constexpr int LDA = C;               // fp32 C x C rows (swizzled, unpadded)
@@ -169,25 +169,29 @@ struct K2Smem {
   static constexpr size_t kGc = GATE == kGateChannel ? sizeof(float) * C * (DK + 4) : 0;
   // (at d_k = 64 in bf16 the write-key tile is too small for X; that block is
   // small anyway)
-  static constexpr bool NOQ = GATE == kGateChannel && PREC != kATQ && kRow >= kFloatCC;
+  static constexpr bool PSCAN = PSCAN_;
+  static_assert(!PSCAN || (sizeof(T) == 2 && GATE != kGateChannel && PREC != kATQ), "see scan_forms_p");
+  static constexpr bool NOQ = PSCAN || (GATE == kGateChannel && PREC != kATQ && kRow >= kFloatCC);
   static constexpr size_t kR2 = NOQ ? 0 : kR1;                      // sQ, later sX
-  static constexpr size_t kR3 = kRow;                               // sKt, later sX (NOQ)
+  static constexpr size_t kR3 = NOQ ? kR1 : kRow;                   // sKt, later sX (NOQ)
   static constexpr size_t kScal = sizeof(float) * 8 * C;    // per-row scalars and the row norms
   static constexpr size_t kSeg = sizeof(float) * 2 * 256;   // preconditioner segment carries
   // the solve's partial products (sY) sit in the write-key tile, dead by the
   // solve, unless the per-channel gate needs them while that tile is live
-  // (its gate prefix) or the tile is too small
-  static constexpr bool YSEP = GATE == kGateChannel || kR3 < kY;
-  static constexpr size_t kYs = YSEP ? kY : 0;
-  static constexpr size_t kTotal = kR1 + kR2 + kR3 + kGc + kYs + kScal + kSeg;
+  // (its gate prefix), X is there or the tile is too small; with PSCAN they
+  // share the segment carries' memory, dead by then too
+  static constexpr bool YSEP = GATE == kGateChannel || NOQ || kR3 < kY;
+  static constexpr size_t kYs = YSEP && !PSCAN ? kY : 0;
+  static constexpr size_t kTail = PSCAN && kY > kSeg ? kY : kSeg;
+  static constexpr size_t kTotal = kR1 + kR2 + kR3 + kGc + kYs + kScal + kTail;
 };
 
 // BWD: also write the operand layouts the backward kernels read (P^T, M^T,
 // write-key rows, write-key rows decayed to the chunk end, (Lam o Q)^T and
 // -(Lam o K)^T; Lam the scalar or per-channel in-chunk decay).
-template <typename T, int DK, int GATE, int PREC, bool BWD, int C>
-__global__ __launch_bounds__(256, 3) void k2_chunk_prep(FwdArgs a) {
-  using SM = K2Smem<T, DK, GATE, PREC, C>;
+template <typename T, int DK, int GATE, int PREC, bool BWD, int C, bool PSCAN>
+__global__ __launch_bounds__(256, PSCAN ? 4 : 3) void k2_chunk_prep(FwdArgs a) {
+  using SM = K2Smem<T, DK, GATE, PREC, C, PSCAN>;
   // row blocks of 16 tokens: wave w owns block w (C = 32: waves 2, 3 only
   // take part in the column-wise phases)
   constexpr int NB = C / 16;
@@ -205,7 +209,8 @@ __global__ __launch_bounds__(256, 3) void k2_chunk_prep(FwdArgs a) {
   T* sKt = reinterpret_cast<T*>(smem + SM::kR1 + SM::kR2);
   float* sGc = reinterpret_cast<float*>(smem + SM::kR1 + SM::kR2 + SM::kR3);
   float* sX = reinterpret_cast<float*>(smem + SM::kR1);   // R2, or with NOQ the write-key tile
-  float* sY = reinterpret_cast<float*>(smem + SM::kR1 + SM::kR2 + (SM::YSEP ? SM::kR3 + SM::kGc : 0));
+  float* sY = reinterpret_cast<float*>(smem + SM::kR1 + SM::kR2 + (SM::YSEP ? SM::kR3 + SM::kGc : 0) +
+                                       (PSCAN ? SM::kScal : 0));
   float* sBeta = reinterpret_cast<float*>(smem + SM::kR1 + SM::kR2 + SM::kR3 + SM::kGc + SM::kYs);
   float* sNrm = sBeta + 7 * C;   // row norms of the normalised write keys
   float* sBp = sBeta + C;
@@ -363,9 +368,9 @@ __global__ __launch_bounds__(256, 3) void k2_chunk_prep(FwdArgs a) {
     constexpr int NSEG = 256 / DK, SEG = C / NSEG;
     const int c = tid % DK, sg = tid / DK, r0 = sg * SEG;
     // this thread's key column over its segment and the rows' decay and
-    // betaP: held in registers for every walk below, or (backward mode,
-    // whose peak is elsewhere and tighter) read from LDS at each walk
-    constexpr bool SEGREG = !BWD;
+    // betaP: held in registers for every walk below, or (backward mode and
+    // PSCAN, whose register budgets are tighter) read from LDS at each walk
+    constexpr bool SEGREG = !BWD && !PSCAN;
     static_assert(SEG % 4 == 0, "segment rows come in float4 groups");
     float kreg[SEGREG ? SEG : 1], egr[SEGREG ? SEG : 1], bpr[SEGREG ? SEG : 1];
     if constexpr (SEGREG) {
@@ -495,7 +500,7 @@ __global__ __launch_bounds__(256, 3) void k2_chunk_prep(FwdArgs a) {
   // NOQ: the query fragments of this lane's A-operand row, straight from
   // HBM, issued here so they arrive during the decayed-row outputs
   Frag8<T> fqr[DK / 32];
-  if (NOQ && (NB == 4 || w < NB)) {
+  if (NOQ && !PSCAN && (NB == 4 || w < NB)) {
     const int r = 16 * w + lr;
     const T* qrow = static_cast<const T*>(a.q) + ((b * a.T + t0 + min(r, n - 1)) * a.H + h) * DK;
 #pragma unroll
@@ -563,7 +568,7 @@ __global__ __launch_bounds__(256, 3) void k2_chunk_prep(FwdArgs a) {
   for (int j = 0; j < NB; ++j) { accA[j] = floatx4{0.f, 0.f, 0.f, 0.f}; accP[j] = accA[j]; }
   if (NB == 4 || w < NB) {
     const int r = 16 * w + lr;  // A-operand row of this lane
-    if (NOQ && r >= n) {   // rows past the sequence end: zero queries
+    if (NOQ && !PSCAN && r >= n) {   // rows past the sequence end: zero queries
 #pragma unroll
       for (int kk = 0; kk < DK / 32; ++kk) fqr[kk] = frag_zero<T>();
     }
@@ -607,11 +612,10 @@ __global__ __launch_bounds__(256, 3) void k2_chunk_prep(FwdArgs a) {
         for (int kk = 0; kk < DK / 32; ++kk) {
           const int c0 = kk * 32 + 8 * lg;
           const Frag8<T> fk = ld8(k2sw(sK, LDK, r, c0));
-          const Frag8<T> fq = NOQ ? fqr[kk] : ld8(k2sw(sQ, LDK, r, c0));
           const Frag8<T> fb = ld8(k2sw(sKt, LDK, t, c0));
           // linear attention (ATQ): no delta-rule interaction, At = 0, T = Diag(beta)
           if (PREC != kATQ) mma(accA[j], fk, fb);
-          mma(accP[j], fq, fb);
+          if (!PSCAN) mma(accP[j], ld8(k2sw(sQ, LDK, r, c0)), fb);
         }
       }
     }
@@ -627,9 +631,9 @@ __global__ __launch_bounds__(256, 3) void k2_chunk_prep(FwdArgs a) {
         const int r = 16 * w + 4 * lg + ii;
         float fac = 1.f;
         if (GATE == kGateScalar) fac = fast_exp(sG[r] - sG[t]);
-        accP[j][ii] = (j <= w && r >= t) ? accP[j][ii] * fac : 0.f;
+        if (!PSCAN) accP[j][ii] = (j <= w && r >= t) ? accP[j][ii] * fac : 0.f;
         accA[j][ii] = (j <= w && r > t) ? sBeta[r] * accA[j][ii] * fac : 0.f;
-        P[r * C + t] = from_f<T>(accP[j][ii]);
+        if (!PSCAN) P[r * C + t] = from_f<T>(accP[j][ii]);
       }
       if (BWD && !ROWS) {
         T* PtT = static_cast<T*>(a.PtT) + a.ci(bh, i) * (int64_t)(C * C);
@@ -793,11 +797,12 @@ __global__ __launch_bounds__(256, 3) void k2_chunk_prep(FwdArgs a) {
       const int r = idx / (C / 8), t0v = (idx % (C / 8)) * 8;
       if (ROWS && r < C / 2 && t0v >= C / 2) {
         // the block right of the diagonal is zero: it carries the chunk's
-        // per-row scalars (lam, w, beta), which reach the scan with M's tile
+        // per-row scalars (lam, w, beta, G), which reach the scan with M's tile
         const int q = r * (C / 16) + (t0v - C / 2) / 8, v = q / (C / 4), t4 = 4 * (q % (C / 4));
         float4 f4 = make_float4(0.f, 0.f, 0.f, 0.f);
         if (v == 2) f4 = *reinterpret_cast<const float4*>(sBeta + t4);
-        else if (v < 2 && GATE == kGateScalar) f4 = *reinterpret_cast<const float4*>((v == 0 ? sLam : sWt) + t4);
+        else if (v < 4 && GATE == kGateScalar)
+          f4 = *reinterpret_cast<const float4*>((v == 0 ? sLam : v == 1 ? sWt : sG) + t4);
         *reinterpret_cast<float4*>(Tout + r * C + t0v) = f4;
         continue;
       }
@@ -1494,8 +1499,16 @@ WsLayout fwd_ws_layout(int64_t BH, int NT, int dk, int dv, int esz, int gate, in
 
 template <typename T, int DK, int GATE, int PREC, bool BWD, int C>
 static hipError_t launch_k2(const FwdArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL((k2_chunk_prep<T, DK, GATE, PREC, BWD, C>), dim3(static_cast<unsigned>(a.BH * a.NT)),
-                     dim3(256), 0, s, a);
+  // (without the per-channel gate the bf16 backward reads what the forward scan does)
+  constexpr bool ROWS = sizeof(T) == 2 && GATE != kGateChannel, B = BWD && !ROWS;
+  const dim3 grid(static_cast<unsigned>(a.BH * a.NT));
+  if constexpr (ROWS && PREC != kATQ) {
+    if (a.forms_p) {
+      hipLaunchKernelGGL((k2_chunk_prep<T, DK, GATE, PREC, B, C, true>), grid, dim3(256), 0, s, a);
+      return hipGetLastError();
+    }
+  }
+  hipLaunchKernelGGL((k2_chunk_prep<T, DK, GATE, PREC, B, C, false>), grid, dim3(256), 0, s, a);
   return hipGetLastError();
 }
 

@@ -216,7 +216,10 @@ static void set_forward_ws(pdn::FwdArgs& a, const pdn::WsLayout& L, const pdn_pr
     a.sumD = reinterpret_cast<float*>(w + L.sumD);
     a.Abound = reinterpret_cast<float*>(w + L.Abound);
   }
-  if (p->io == PDN_BF16) a.Kd = w + L.KtG;
+  if (p->io == PDN_BF16) {
+    a.Kd = w + L.KtG;
+    a.forms_p = pdn::scan_forms_p(a.BH, a.NT, a.dv, a.gate, a.precond, L.split);
+  }
   else a.KtG = w + L.KtG;
   a.Tm = w + L.Tm;
   a.Pm = w + L.Pm;

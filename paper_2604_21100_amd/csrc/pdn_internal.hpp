@@ -55,6 +55,7 @@ struct FwdArgs {
   float* sumD;    // [BH, NT]       in-chunk sum of gP (log of the decay)
   float* Abound;  // [BH, NT+1, dk] preconditioner state before each chunk
   void* KtG;      // fp32: [BH, NT, dk, C] (Kt * Gamma)^T per chunk
+  bool forms_p;   // bf16: the scan forms P (scan_forms_p)
   void* Kd;       // bf16: [BH, Tpad, dk] write-key rows (per-channel gate: w_r o Kt rows)
   void* Tm;       // [BH, NT, C, C]  fp32: T = M Diag(beta); bf16: M = (I + At)^{-1}
   void* Pm;       // [BH, NT, C, C]  causal (Q*Lam)(Kt/Lam)^T, io dtype
@@ -115,6 +116,20 @@ inline ScanSplit scan_split(int64_t BH, int NT, int dk, int dv) {
   }
   if (r.S < 3) r = ScanSplit{1, NT};
   return r;
+}
+
+// Whether the bf16 state scan forms P itself from the query rows and write
+// keys it holds, rather than the chunk preparation writing it (which then must
+// read the queries): 100 to 133 MB less traffic at the 1B layer, for 40 more
+// MFMA and 48 KB more LDS reads a step in the scan.  Worth it where the scan
+// waits for memory: its slabs fill the chip and its runs are long.  Forward
+// passes, d = 128, scalar gate, formed against written, us: 64 heads of 4096
+// tokens 206 / 240; 64 of 777 57 / 55; 16 of 32768 (split, 192 workgroups) a
+// scan pass 327 / 269, two of them against 50 saved in the preparation.
+// (The per-channel gate's P has its decay inside the contraction, and linear
+// attention's preparation rewrites the queries anyway.)
+inline bool scan_forms_p(int64_t BH, int NT, int dv, int gate, int precond, const ScanSplit& sp) {
+  return gate != kGateChannel && precond != kATQ && sp.S < 3 && BH * (dv / 32) >= kScanCUs && NT >= 32;
 }
 
 // Backward-only arguments and workspace (the forward recompute uses f).

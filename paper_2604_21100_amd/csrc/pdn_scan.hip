@@ -294,16 +294,18 @@ struct FwdLoader {
   }
 };
 
-// An output wave's query and P rows (row tile ow of the chunk) as loaded: a
+// An output wave's query and P rows (row tile ow of the chunk).  As loaded, a
 // fragment pair (two 64-byte halves of a row's 128 bytes) comes as two rows'
 // whole lines, lanes m even / odd taking the halves of row m & ~1 in the
-// first and of row m | 1 in the second, and is put in order where it is used
-// (take_pair).  The memory path's cost goes by the lines an instruction
+// first and of row m | 1 in the second, and is put in order where it is first
+// used (take_pair).  The memory path's cost goes by the lines an instruction
 // touches: 8 this way, 16 with a fragment's own lanes.
-template <int DK, int GATE, int C>
+// PSCAN: P is formed here from the query rows and the stage's write keys
+// (scan_forms_p), else it is read.
+template <int DK, int GATE, int C, bool LA>
 struct OutRows {
   bf16x8 q[DK / 32], p[C / 32];
-  float lam;
+  float g;   // scalar gate: G_r of this lane's row
 };
 
 // a, b: the pair as loaded -> the fragments of row m's first and second half
@@ -329,23 +331,23 @@ __device__ __forceinline__ bf16x8 buf_get16(__amdgpu_buffer_rsrc_t r, uint32_t o
 template <int DK, int GATE, int C, bool LA>
 struct OutLanes {
   static constexpr bool WS = GATE == kGateChannel || LA;
-  uint32_t q, qrow, p, lam, o;
+  uint32_t q, qrow, p, g, o;
   bool odd;
   __device__ __forceinline__ OutLanes(const ChunkCursor& c, int ow, int l) {
-    const int m = l & 15, g = l >> 4, r = 16 * ow + m;
+    const int m = l & 15, lg = l >> 4, r = 16 * ow + m;
     odd = m & 1;
     qrow = WS ? DK * 2 : c.hd;
-    q = (r & ~1) * qrow + 64 * (m & 1) + 16 * g;
-    p = C == 64 ? (r & ~1) * (C * 2) + 64 * (m & 1) + 16 * g : r * (C * 2) + 16 * g;
-    lam = (r / (C / 4)) * (2 * C) + C + (r % (C / 4)) * 4;   // lam_r, among the scalars in M
-    o = r * c.hv + 16 * g;
+    q = (r & ~1) * qrow + 64 * (m & 1) + 16 * lg;
+    p = C == 64 ? (r & ~1) * (C * 2) + 64 * (m & 1) + 16 * lg : r * (C * 2) + 16 * lg;
+    g = (12 + r / (C / 4)) * (2 * C) + C + (r % (C / 4)) * 4;   // G_r, among the scalars in M
+    o = r * c.hv + 16 * lg;
   }
 };
 
 // the next chunk's rows (rows past the sequence end are zero; past the run:
 // empty ranges, no traffic)
-template <int DK, int GATE, int C, bool LA>
-__device__ __forceinline__ void out_load(OutRows<DK, GATE, C>& f, ChunkCursor& c, const OutLanes<DK, GATE, C, LA>& o) {
+template <bool PSCAN, int DK, int GATE, int C, bool LA>
+__device__ __forceinline__ void out_load(OutRows<DK, GATE, C, LA>& f, ChunkCursor& c, const OutLanes<DK, GATE, C, LA>& o) {
   constexpr int KK = DK / 32, SB = C / 32;
   constexpr bool WS = OutLanes<DK, GATE, C, LA>::WS;
   const int n = c.rows<C>();
@@ -357,21 +359,67 @@ __device__ __forceinline__ void out_load(OutRows<DK, GATE, C>& f, ChunkCursor& c
     f.q[kk] = buf_get16(rq, o.q + 64 * kk);
     f.q[kk + 1] = buf_get16(rq, o.q + 64 * kk + o.qrow);
   }
+  if (!PSCAN)
 #pragma unroll
-  for (int s = 0; s < SB; ++s) f.p[s] = buf_get16(rp, o.p + s * (C * 2));
+    for (int s = 0; s < SB; ++s) f.p[s] = buf_get16(rp, o.p + s * (C * 2));
   if (GATE == kGateScalar)
-    f.lam = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rm, static_cast<int>(o.lam), 0, 0));
+    f.g = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rm, static_cast<int>(o.g), 0, 0));
   c.q += WS ? c.heads * (C * DK * 2) : C * static_cast<int64_t>(c.hd);
   c.p += c.heads * (C * C * 2);
   c.m += c.heads * (C * C * 2);
   c.next<C>();
 }
 
+// P of this wave's rows from the write keys of the stage at sg: P^T tiles
+// (rows t = 32 s + 8 (m >> 2) + 4 u + (m & 3)) whose accumulators are the right
+// operand of P E.  ps: where the chunk's P goes for the backward, or null.
+template <int DK, int GATE, int C, bool LA>
+__device__ __forceinline__ void form_p(OutRows<DK, GATE, C, LA>& f, const OutLanes<DK, GATE, C, LA>& o, const lds_char* sg,
+                                       int ow, int l, char* ps) {
+  using L = FwdLds<DK, GATE, C>;
+  constexpr int KK = DK / 32, SB = C / 32, RK = DK * 2;
+  const int m = l & 15, g = l >> 4, r = 16 * ow + m;
+#pragma unroll
+  for (int kk = 0; kk < KK; kk += 2) take_pair(f.q[kk], f.q[kk + 1], o.odd);
+#pragma unroll
+  for (int s = 0; s < SB; ++s) {
+    floatx4 acc[2] = {floatx4{0.f, 0.f, 0.f, 0.f}, floatx4{0.f, 0.f, 0.f, 0.f}};
+    if (2 * s <= ow) {   // (the block right of the diagonal is zero)
+      bf16x8 fk[KK][2];
+      floatx4 gt[2];
+#pragma unroll
+      for (int kk = 0; kk < KK; ++kk)
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+          fk[kk][u] = lds_frag(sg + L::oKt + tile_off<DK / 8>(8 * (m >> 2) + (m & 3), 4 * kk + g) + (32 * s + 4 * u) * RK);
+      if (GATE == kGateScalar)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) gt[u] = lds_f4(sg + L::oM + scal_off<C>(3, 8 * s + 2 * g + u));
+      reads_done();
+#pragma unroll
+      for (int kk = 0; kk < KK; ++kk)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) acc[u] = mfma(fk[kk][u], f.q[kk], acc[u]);
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int t = 32 * s + 8 * g + 4 * u + i;
+          const float fac = GATE == kGateScalar ? fast_exp(f.g - gt[u][i]) : 1.f;
+          acc[u][i] = r >= t ? acc[u][i] * fac : 0.f;
+        }
+    }
+    f.p[s] = pack8(acc[0], acc[1]);
+    // (the reverse scan does not read the block right of the diagonal)
+    if (ps && 2 * s <= ow) *reinterpret_cast<bf16x8*>(ps + r * (C * 2) + 64 * s + 16 * g) = f.p[s];
+  }
+}
+
 // O rows of the chunk at ob (n valid rows) from the S and E fragments of its
 // step, transposed products (rows are value columns), so a lane holds eight
 // adjacent columns of a row.
-template <int DK, int GATE, int C, bool LA>
-__device__ __forceinline__ void out_store(OutRows<DK, GATE, C>& f, const OutLanes<DK, GATE, C, LA>& o, char* ob, int n,
+template <bool PSCAN, int DK, int GATE, int C, bool LA>
+__device__ __forceinline__ void out_store(OutRows<DK, GATE, C, LA>& f, const OutLanes<DK, GATE, C, LA>& o, char* ob, int n,
                                           uint32_t hv, float scale, const lds_char* sS, const lds_char* sE, int l) {
   constexpr int KK = DK / 32, SB = C / 32;
   bf16x8 fs[2][KK], fe[2][SB];
@@ -383,17 +431,20 @@ __device__ __forceinline__ void out_store(OutRows<DK, GATE, C>& f, const OutLane
     for (int s = 0; s < SB; ++s) fe[v][s] = lds_frag(sE + (v * SB + s) * 1024 + l * 16);
   }
   reads_done();
+  if (!PSCAN) {
 #pragma unroll
-  for (int kk = 0; kk < KK; kk += 2) take_pair(f.q[kk], f.q[kk + 1], o.odd);
-  if (SB == 2) take_pair(f.p[0], f.p[SB - 1], o.odd);
+    for (int kk = 0; kk < KK; kk += 2) take_pair(f.q[kk], f.q[kk + 1], o.odd);
+    if (SB == 2) take_pair(f.p[0], f.p[SB - 1], o.odd);
+  }
   floatx4 acc[2] = {floatx4{0.f, 0.f, 0.f, 0.f}, floatx4{0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
   for (int kk = 0; kk < KK; ++kk)
 #pragma unroll
     for (int v = 0; v < 2; ++v) acc[v] = mfma(fs[v][kk], f.q[kk], acc[v]);
   if (GATE == kGateScalar) {
-    acc[0] *= f.lam;
-    acc[1] *= f.lam;
+    const float lam = fast_exp(f.g);
+    acc[0] *= lam;
+    acc[1] *= lam;
   }
 #pragma unroll
   for (int s = 0; s < SB; ++s)
@@ -424,7 +475,7 @@ __device__ __forceinline__ void keep_store(const FwdArgs& a, int i, const RunCtx
       frag_major_row<C / 32>(sE, f, hh, l);
 }
 
-template <int DK, int GATE, bool SAVE, bool OUT, bool LA, int C>
+template <int DK, int GATE, bool SAVE, bool OUT, bool LA, int C, bool PSCAN>
 __device__ __forceinline__ void fwd_run(const FwdArgs& a, const RunCtx& x, int seg, int pv0, lds_char* sm) {
   using L = FwdLds<DK, GATE, C>;
   constexpr int KK = L::KK;
@@ -498,39 +549,52 @@ __device__ __forceinline__ void fwd_run(const FwdArgs& a, const RunCtx& x, int s
     const OutLanes<DK, GATE, C, LA> lanes(c, ow, l);
     char* ob = static_cast<char*>(a.o) + ((x.b * a.T + static_cast<int64_t>(x.c0) * C) * a.H + x.h) * a.dv * 2 + x.v0 * 2;
     int64_t left = c.tokens;
-    OutRows<DK, GATE, C> q[3];
-    if (OUT) {
-      out_load<DK, GATE, C, LA>(q[0], c, lanes);
-      out_load<DK, GATE, C, LA>(q[1], c, lanes);
+    constexpr bool ROWS = OUT || (SAVE && PSCAN);   // the query rows are needed
+    char* ps = SAVE && PSCAN ? static_cast<char*>(a.Pm) + a.ci(x.bh, x.c0) * (C * C * 2) : nullptr;
+    OutRows<DK, GATE, C, LA> q[4];
+    if (ROWS) {
+      out_load<PSCAN, DK, GATE, C, LA>(q[0], c, lanes);
+      out_load<PSCAN, DK, GATE, C, LA>(q[1], c, lanes);
     }
+    const lds_char* sg = sm;   // the step's stage
+    // step j: load chunk j + 2's rows, form P of chunk j (its write keys are
+    // in the step's stage)
+    auto begin = [&](OutRows<DK, GATE, C, LA>& next, OutRows<DK, GATE, C, LA>& f) {
+      if (ROWS) out_load<PSCAN, DK, GATE, C, LA>(next, c, lanes);
+      if (ROWS && PSCAN) {
+        form_p<DK, GATE, C, LA>(f, lanes, sg, ow, l, ps);
+        if (SAVE) ps += a.BH * (C * C * 2);
+      }
+      sg = sg == sm + 2 * L::kStage ? sm : sg + L::kStage;
+    };
     // chunk c0 + j, a step after its own
-    auto finish = [&](OutRows<DK, GATE, C>& f, int j) {
+    auto finish = [&](OutRows<DK, GATE, C, LA>& f, int j) {
       const lds_char* sS = sm + L::oS + (j & 1) * L::kS;
       const lds_char* sE = sm + L::oE + (j & 1) * L::kE;
       if (OUT) {
-        out_store<DK, GATE, C, LA>(f, lanes, ob, static_cast<int>(min<int64_t>(C, left)), c.hv, a.scale, sS, sE, l);
+        out_store<PSCAN, DK, GATE, C, LA>(f, lanes, ob, static_cast<int>(min<int64_t>(C, left)), c.hv, a.scale, sS, sE, l);
         ob += C * static_cast<int64_t>(c.hv);
         left -= C;
       }
       if (SAVE) keep_store<DK, C>(a, x.c0 + j, x, sS, sE, ow, l);
     };
     lds_sync();   // the first chunk's tiles are in
+    begin(q[2], q[0]);
     lds_sync();   // step 0
-    // step j finishes chunk j - 1 (set (j - 1) mod 3), after issuing the
-    // loads of chunk j + 1 (so they queue ahead of the step's stores)
+    // step j (chunk j's rows in set j mod 4): as above, and chunk j - 1's output
     int j = 1;
-    for (; j + 2 < cnt; j += 3) {
+    for (; j + 3 < cnt; j += 4) {
 #pragma unroll
-      for (int d = 0; d < 3; ++d) {
-        if (OUT) out_load<DK, GATE, C, LA>(q[(d + 2) % 3], c, lanes);
+      for (int d = 0; d < 4; ++d) {
+        begin(q[(d + 3) % 4], q[(d + 1) % 4]);
         if (KEEP) finish(q[d], j + d - 1);
         lds_sync();
       }
     }
 #pragma unroll
-    for (int d = 0; d < 3; ++d) {
+    for (int d = 0; d < 4; ++d) {
       if (j + d < cnt) {
-        if (OUT && d < 1) out_load<DK, GATE, C, LA>(q[(d + 2) % 3], c, lanes);
+        begin(q[(d + 3) % 4], q[(d + 1) % 4]);
         if (KEEP) finish(q[d], j + d - 1);
         lds_sync();
       } else if (j + d == cnt) {
@@ -559,7 +623,7 @@ __device__ __forceinline__ void fwd_run(const FwdArgs& a, const RunCtx& x, int s
   }
 }
 
-template <int DK, int GATE, bool SAVE, bool OUT, bool LA, int C>
+template <int DK, int GATE, bool SAVE, bool OUT, bool LA, int C, bool PSCAN>
 __global__ __launch_bounds__(scan_threads(C), 2) void fwd_scan(FwdArgs a) {
   using L = FwdLds<DK, GATE, C>;
   __shared__ __attribute__((aligned(1024))) char smem[L::kTotal];
@@ -600,37 +664,47 @@ __global__ __launch_bounds__(scan_threads(C), 2) void fwd_scan(FwdArgs a) {
   x.v0 = x.probe ? 0 : slab * kCols;
   const int pv0 = x.probe ? (slab - nslab) * kCols : 0;
   // middle segments of the first pass need only their end states
-  if (a.seg_phase == 1 && seg > 0) fwd_run<DK, GATE, false, false, LA, C>(a, x, seg, pv0, sm);
-  else fwd_run<DK, GATE, SAVE, OUT, LA, C>(a, x, seg, pv0, sm);
+  if (a.seg_phase == 1 && seg > 0) fwd_run<DK, GATE, false, false, LA, C, PSCAN>(a, x, seg, pv0, sm);
+  else fwd_run<DK, GATE, SAVE, OUT, LA, C, PSCAN>(a, x, seg, pv0, sm);
 }
 
-template <int DK, int GATE, bool SAVE, bool OUT, bool LA, int C>
+template <int DK, int GATE, bool SAVE, bool OUT, bool LA, int C, bool PSCAN>
 hipError_t launch_typed(const FwdArgs& a0, hipStream_t s) {
   FwdArgs a = a0;
   const int nslab = a.dv / kCols, npslab = DK / kCols;
   auto grid = [&](int nrole) { return dim3(static_cast<unsigned>(((a.BH + 7) / 8) * 8 * nrole)); };
   if (a.seg_cnt < 3) {
     a.seg_phase = 0;
-    hipLaunchKernelGGL((fwd_scan<DK, GATE, SAVE, OUT, LA, C>), grid(nslab), dim3(scan_threads(C)), 0, s, a);
+    hipLaunchKernelGGL((fwd_scan<DK, GATE, SAVE, OUT, LA, C, PSCAN>), grid(nslab), dim3(scan_threads(C)), 0, s, a);
     return hipGetLastError();
   }
   const int S = a.seg_cnt;
   a.seg_phase = 1;
-  hipLaunchKernelGGL((fwd_scan<DK, GATE, SAVE, OUT, LA, C>), grid(nslab + (S - 2) * (nslab + npslab)), dim3(scan_threads(C)), 0, s,
+  hipLaunchKernelGGL((fwd_scan<DK, GATE, SAVE, OUT, LA, C, PSCAN>), grid(nslab + (S - 2) * (nslab + npslab)), dim3(scan_threads(C)), 0, s,
                      a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if ((e = launch_seg_compose(a, false, s)) != hipSuccess) return e;
   a.seg_phase = 3;
-  hipLaunchKernelGGL((fwd_scan<DK, GATE, SAVE, OUT, LA, C>), grid((S - 1) * nslab), dim3(scan_threads(C)), 0, s, a);
+  hipLaunchKernelGGL((fwd_scan<DK, GATE, SAVE, OUT, LA, C, PSCAN>), grid((S - 1) * nslab), dim3(scan_threads(C)), 0, s, a);
   return hipGetLastError();
+}
+
+template <int DK, int GATE, int C, bool PSCAN>
+hipError_t launch_save(const FwdArgs& a, bool save, bool out, hipStream_t s) {
+  if (save)
+    return out ? launch_typed<DK, GATE, true, true, false, C, PSCAN>(a, s)
+               : launch_typed<DK, GATE, true, false, false, C, PSCAN>(a, s);
+  return launch_typed<DK, GATE, false, true, false, C, PSCAN>(a, s);
 }
 
 template <int DK, int GATE, int C>
 hipError_t launch_mode(const FwdArgs& a, bool save, bool out, hipStream_t s) {
-  if (a.precond == kATQ) return launch_typed<DK, GATE, false, true, true, C>(a, s);
-  if (save) return out ? launch_typed<DK, GATE, true, true, false, C>(a, s) : launch_typed<DK, GATE, true, false, false, C>(a, s);
-  return launch_typed<DK, GATE, false, true, false, C>(a, s);
+  if (a.precond == kATQ) return launch_typed<DK, GATE, false, true, true, C, false>(a, s);
+  if constexpr (GATE != kGateChannel) {
+    if (a.forms_p) return launch_save<DK, GATE, C, true>(a, save, out, s);
+  }
+  return launch_save<DK, GATE, C, false>(a, save, out, s);
 }
 
 template <int DK, int C>

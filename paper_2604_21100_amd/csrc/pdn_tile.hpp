@@ -104,8 +104,14 @@ struct RunCtx {
 };
 
 // chunk rows as a raw buffer (0 bytes: reads are zeros and cost no traffic)
+// (base and size are the same in every lane; said outright, or a descriptor
+// the compiler cannot prove uniform costs a loop over its distinct values)
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_rsrc(const char* base, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base), 0, static_cast<int>(bytes), kBufWord3);
+  const uint64_t p = reinterpret_cast<uint64_t>(base);
+  const uint64_t lo = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(p)));
+  const uint64_t hi = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(p >> 32)));
+  return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(hi << 32 | lo), 0,
+                                           __builtin_amdgcn_readfirstlane(static_cast<int>(bytes)), kBufWord3);
 }
 
 // Memory to LDS, 1 KB (64 lanes of 16 bytes) an instruction: unit u of a tile
@@ -122,7 +128,7 @@ __device__ __forceinline__ void unit_copy(__amdgpu_buffer_rsrc_t r, uint32_t off
                                            0, 0, 0);
 }
 
-// The chunk's per-row scalars (0: lam, 1: w, 2: beta) ride in the block of M
+// The chunk's per-row scalars (0: lam, 1: w, 2: beta, 3: G) ride in the block of M
 // right of the diagonal, which is zero (rows 0 .. C/2 - 1, columns C/2 ..):
 // offset in the M tile of the four values of rows 4 q .. 4 q + 3.
 template <int C>
