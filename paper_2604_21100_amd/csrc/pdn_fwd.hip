@@ -509,13 +509,36 @@ __global__ __launch_bounds__(256, PSCAN ? 4 : 3) void k2_chunk_prep(FwdArgs a) {
   if (GATE == kGateChannel) {
     // Lam o Q and Lam o K (Lam_r = exp(G_r) per channel; Q the query the
     // scan reads: q, or for ATQ the preconditioned query): the rows the
-    // scan reads, rounded to io as the scan would round them, and for the
-    // backward their transposes (Lam o Q)^T and -(Lam o K)^T, [dk][C].  A
-    // thread takes 8 rows x 4 channels, so each exponential serves all four
-    // outputs.
+    // scans read, rounded to io, and for the fp32 backward their transposes
+    // (Lam o Q)^T and -(Lam o K)^T, [dk][C]: there a thread takes 8 rows x 4
+    // channels, so each exponential serves all four outputs.
     T* ql = static_cast<T*>(a.QL) + a.ci(bh, i) * (C * DK);
     T* kl = static_cast<T*>(a.KL) + a.ci(bh, i) * (C * DK);
     const T* qg = static_cast<const T*>(a.q) + ((b * a.T + t0) * a.H + h) * DK;
+    if constexpr (ROWS) {
+      // rows only: 8 channels of a row a thread, so loads and stores are whole
+      // rows of 16-byte vectors
+#pragma unroll
+      for (int jj = 0; jj < (C * VPR) / 256; ++jj) {
+        const int idx = tid + 256 * jj;
+        const int r = idx / VPR, c0 = (idx % VPR) * VEC;
+        Frag8<T> fq = NOQ ? ld8(qg + static_cast<int64_t>(min(r, n - 1)) * a.H * DK + c0) : ld8(k2sw(sQ, LDK, r, c0));
+        Frag8<T> fk = ld8(k2sw(sK, LDK, r, c0));
+#pragma unroll
+        for (int e4 = 0; e4 < 8; e4 += 4) {
+          const float4 g4 = *reinterpret_cast<const float4*>(k2swf(sGc, DK + 4, r, c0 + e4));
+          const float gv[4] = {g4.x, g4.y, g4.z, g4.w};
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float lam = fast_exp(gv[e]);
+            fq.set(e4 + e, lam * ((NOQ && r >= n) ? 0.f : fq.get(e4 + e)));
+            fk.set(e4 + e, lam * fk.get(e4 + e));
+          }
+        }
+        st8(ql + r * DK + c0, fq);
+        st8(kl + r * DK + c0, fk);
+      }
+    } else {
     using V4 = typename Vec4<T>::type;
     constexpr int RB = C / 8, NTILE = RB * (DK / 4);
 #pragma unroll
@@ -550,7 +573,7 @@ __global__ __launch_bounds__(256, PSCAN ? 4 : 3) void k2_chunk_prep(FwdArgs a) {
         st4<T>(ql + r * DK + c0, qo[0], qo[1], qo[2], qo[3]);
         st4<T>(kl + r * DK + c0, ko[0], ko[1], ko[2], ko[3]);
       }
-      if (BWD && !ROWS) {
+      if (BWD) {
         T* QlT = static_cast<T*>(a.QlT) + a.ci(bh, i) * (int64_t)(DK * C);
         T* KnT = static_cast<T*>(a.KnT) + a.ci(bh, i) * (int64_t)(DK * C);
 #pragma unroll
@@ -559,6 +582,7 @@ __global__ __launch_bounds__(256, PSCAN ? 4 : 3) void k2_chunk_prep(FwdArgs a) {
           st8(KnT + (c0 + e) * C + r0, fk[e]);
         }
       }
+    }
     }
   }
 
@@ -679,12 +703,31 @@ __global__ __launch_bounds__(256, PSCAN ? 4 : 3) void k2_chunk_prep(FwdArgs a) {
   }
   // ---- decayed write keys: rows (bf16, per-channel gate), transposed per
   // chunk (fp32: (Kt * Lam_C / Lam_t)^T)
-  if (GATE == kGateChannel) {
+  if (GATE == kGateChannel && ROWS) {
+    // w_t o Kt rows, w_t = exp(G_{C-1} - G_t) per channel, 8 channels of a
+    // row a thread
+    T* Kw = static_cast<T*>(a.Kd) + a.ci(bh, i) * (C * DK);
+#pragma unroll
+    for (int jj = 0; jj < (C * VPR) / 256; ++jj) {
+      const int idx = tid + 256 * jj;
+      const int r = idx / VPR, c0 = (idx % VPR) * VEC;
+      Frag8<T> f = ld8(k2sw(sKt, LDK, r, c0));
+#pragma unroll
+      for (int e4 = 0; e4 < 8; e4 += 4) {
+        const float4 ge = *reinterpret_cast<const float4*>(k2swf(sGc, DK + 4, C - 1, c0 + e4));
+        const float4 g4 = *reinterpret_cast<const float4*>(k2swf(sGc, DK + 4, r, c0 + e4));
+        const float gd[4] = {ge.x - g4.x, ge.y - g4.y, ge.z - g4.z, ge.w - g4.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) f.set(e4 + e, fast_exp(gd[e]) * f.get(e4 + e));
+      }
+      st8(Kw + r * DK + c0, f);
+    }
+  } else if (GATE == kGateChannel) {
     // w_t = exp(G_{C-1} - G_t) per channel, 8 rows x 4 channels a thread:
     // each factor serves the transposed tile for the scan and, for the
     // backward, the row-major w o Kt
     T* Kout = static_cast<T*>(a.KtG) + a.ci(bh, i) * (int64_t)(DK * C);
-    T* Kw = static_cast<T*>(ROWS ? a.Kd : a.Kw) + a.ci(bh, i) * (C * DK);
+    T* Kw = static_cast<T*>(a.Kw) + a.ci(bh, i) * (C * DK);
     using V4 = typename Vec4<T>::type;
     constexpr int RB = C / 8, NTILE = RB * (DK / 4);
 #pragma unroll
@@ -707,11 +750,10 @@ __global__ __launch_bounds__(256, PSCAN ? 4 : 3) void k2_chunk_prep(FwdArgs a) {
           wv[e] = fast_exp(gend[e] - gv[e]) * to_f(kt4[e]);
           f[e].set(s2, wv[e]);
         }
-        if (BWD || ROWS) st4<T>(Kw + t * DK + c0, wv[0], wv[1], wv[2], wv[3]);
+        if (BWD) st4<T>(Kw + t * DK + c0, wv[0], wv[1], wv[2], wv[3]);
       }
-      if (!ROWS)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) st8(Kout + (c0 + e) * C + r0, f[e]);
+      for (int e = 0; e < 4; ++e) st8(Kout + (c0 + e) * C + r0, f[e]);
     }
   } else if (!ROWS) {
     T* Kout = static_cast<T*>(a.KtG) + a.ci(bh, i) * (int64_t)(DK * C);
