@@ -477,6 +477,17 @@ struct RowStage {
     if constexpr (kPer > 2) get(2, v2);
     if constexpr (kPer > 3) get(3, v3);
   }
+  // the same of a saved-rows tensor (saved_idx)
+  __device__ __forceinline__ void load_saved(const T* src, int tid) {
+    auto get = [&](int j, float4& x) {
+      const int idx = tid + 256 * j, r = idx / kVpr, cv = idx % kVpr;
+      x = *reinterpret_cast<const float4*>(src + saved_idx<T, C, DD>(r, cv * kVec));
+    };
+    get(0, v0);
+    if constexpr (kPer > 1) get(1, v1);
+    if constexpr (kPer > 2) get(2, v2);
+    if constexpr (kPer > 3) get(3, v3);
+  }
   __device__ __forceinline__ void store(T* dst, int tid) const {
     constexpr int LD = DD + 8;
     auto put = [&](int j, float4 x) {
@@ -564,17 +575,18 @@ __device__ __forceinline__ void load_pair_regs(HeldTile<T, HC, C>& now, HeldTile
 // One phase-B pass's rows of the chunk-start state S^T and of its adjoint
 // ([HC][DV] each), loaded a pass ahead into named registers and written to
 // LDS ([HC][DV + 8], bank-spread) when the pass starts.
-template <typename T, int HC, int DV>
+template <typename T, int HC, int DK, int DV>
 struct StateRows {
   static constexpr int kVec = 16 / static_cast<int>(sizeof(T)), kVpr = DV / kVec;
   static constexpr int kPer = HC * kVpr / 256;
   static_assert(HC * kVpr % 256 == 0 && (kPer == 1 || kPer == 2), "one or two vectors per thread");
   float4 h0, h1, d0, d1;
-  __device__ __forceinline__ void load(const T* Hs, const T* dHs, int tid) {
+  __device__ __forceinline__ void load(const T* Hs, const T* dHs, int c0, int tid) {
     auto get = [&](int j, float4& h, float4& d) {
       const int idx = tid + 256 * j, c = idx / kVpr, cv = idx % kVpr;
-      h = *reinterpret_cast<const float4*>(Hs + c * DV + cv * kVec);
-      d = *reinterpret_cast<const float4*>(dHs + c * DV + cv * kVec);
+      const int o = saved_idx<T, DK, DV>(c0 + c, cv * kVec);
+      h = *reinterpret_cast<const float4*>(Hs + o);
+      d = *reinterpret_cast<const float4*>(dHs + o);
     };
     get(0, h0, d0);
     if constexpr (kPer == 2) get(1, h1, d1);
@@ -740,12 +752,12 @@ __global__ __launch_bounds__(256, 2) void p12_chunk_grads(BwdArgs ba) {
 #pragma unroll
     for (int kk = 0; kk < KV; ++kk) {
       const uint32_t o = (rc * static_cast<uint32_t>(HV) + 32 * kk + 8 * lg) * E;
-      const uint32_t ow = (static_cast<uint32_t>((rows ? ra : 0) * DV) + 32 * kk + 8 * lg) * E;
+      const uint32_t ow = static_cast<uint32_t>(saved_idx<T, C, DV>(rows ? ra : 0, 32 * kk + 8 * lg)) * E;
       fO[kk] = ld8(at_bytes(dob, o));
       fV[kk] = ld8(at_bytes(vb, o));
       fZ[kk] = ld8(at_bytes(zb, ow));
     }
-    stE.load(eb, tid);
+    stE.load_saved(eb, tid);
   }
   // per-row scalars, with the tiles: every wave loads the chunk's rows and
   // stores the same values (no branch, so the loads issue with the rest)
@@ -774,8 +786,8 @@ __global__ __launch_bounds__(256, 2) void p12_chunk_grads(BwdArgs ba) {
     }
   }
   // phase B's first state rows: in flight through the rest of phase A
-  StateRows<T, HC, DV> srows;
-  srows.load(static_cast<const T*>(a.Hs) + cs, static_cast<const T*>(ba.dHs) + cs, tid);
+  StateRows<T, HC, DK, DV> srows;
+  srows.load(static_cast<const T*>(a.Hs) + cs, static_cast<const T*>(ba.dHs) + cs, 0, tid);
   // and its transposed write-key, query and key tiles
   const T* qtile = static_cast<const T*>(a.q) + (b * a.T + t0) * HD + h * DK;
   const T* ktile = static_cast<const T*>(a.k) + (b * a.T + t0) * HD + h * DK;
@@ -914,7 +926,7 @@ __global__ __launch_bounds__(256, 2) void p12_chunk_grads(BwdArgs ba) {
     srows.store(sS, sdS, tid);
     if (GATE == kGateScalar) {   // sum(dS' o S) over this pass's rows
       red += srows.template dot<0>();
-      if constexpr (StateRows<T, HC, DV>::kPer == 2) red += srows.template dot<1>();
+      if constexpr (StateRows<T, HC, DK, DV>::kPer == 2) red += srows.template dot<1>();
     }
     // transposed Kt, Q, K tiles (loaded during an earlier pass)
     if ((p & 1) == 0) {
@@ -929,7 +941,7 @@ __global__ __launch_bounds__(256, 2) void p12_chunk_grads(BwdArgs ba) {
       // the next pass's state rows load during this pass (the last pass
       // reloads its own rows, unused)
       const int cn = min(p + 1, NPASS - 1) * HC;
-      srows.load(static_cast<const T*>(a.Hs) + cs + cn * DV, static_cast<const T*>(ba.dHs) + cs + cn * DV, tid);
+      srows.load(static_cast<const T*>(a.Hs) + cs, static_cast<const T*>(ba.dHs) + cs, cn, tid);
       if ((p & 1) == 1 && p + 1 < NPASS) {   // the next two passes' tiles
         load_pair_regs<T, HC, C>(tQ, hQ, qtile + cn, HD, n, tid);
         load_pair_regs<T, HC, C>(tK, hK, ktile + cn, HD, n, tid);
@@ -1111,7 +1123,7 @@ __global__ __launch_bounds__(256, 2) void p12c_chunk_grads(BwdArgs ba) {
 #pragma unroll
     for (int kk = 0; kk < KV; ++kk) {
       const uint32_t o = (rc * static_cast<uint32_t>(HV) + 32 * kk + 8 * lg) * E;
-      const uint32_t ow = (static_cast<uint32_t>((rows ? ra : 0) * DV) + 32 * kk + 8 * lg) * E;
+      const uint32_t ow = static_cast<uint32_t>(saved_idx<T, C, DV>(rows ? ra : 0, 32 * kk + 8 * lg)) * E;
       fO[kk] = ld8(at_bytes(dob, o));
       fV[kk] = ld8(at_bytes(vb, o));
       fZ[kk] = ld8(at_bytes(zb, ow));
@@ -1127,10 +1139,10 @@ __global__ __launch_bounds__(256, 2) void p12c_chunk_grads(BwdArgs ba) {
     if (lg == 0 && rows) sZV[ra] = zv;
   }
   RowStage<T, DV, C> stE;
-  stE.load(static_cast<const T*>(a.Er) + rv, tid);
+  stE.load_saved(static_cast<const T*>(a.Er) + rv, tid);
   // phase B's first state rows: in flight through the rest of phase A
-  StateRows<T, HC, DV> srows;
-  srows.load(static_cast<const T*>(a.Hs) + cs, static_cast<const T*>(ba.dHs) + cs, tid);
+  StateRows<T, HC, DK, DV> srows;
+  srows.load(static_cast<const T*>(a.Hs) + cs, static_cast<const T*>(ba.dHs) + cs, 0, tid);
   // and its transposed write-key, query and key tiles
   const T* qtile = static_cast<const T*>(a.q) + (b * a.T + t0) * HD + h * DK;
   const T* ktile = static_cast<const T*>(a.k) + (b * a.T + t0) * HD + h * DK;
@@ -1222,7 +1234,7 @@ __global__ __launch_bounds__(256, 2) void p12c_chunk_grads(BwdArgs ba) {
     {
       // sum_v S dS' per channel of the pass, from the rows just stored: the
       // kVpr lanes of a channel are adjacent
-      using SR = StateRows<T, HC, DV>;
+      using SR = StateRows<T, HC, DK, DV>;
       auto chan = [&](float r2, int jj) {
 #pragma unroll
         for (int off = 1; off < SR::kVpr; off <<= 1) r2 += __shfl_xor(r2, off, 64);
@@ -1265,7 +1277,7 @@ __global__ __launch_bounds__(256, 2) void p12c_chunk_grads(BwdArgs ba) {
       // the next pass's state rows load during this pass (the last pass
       // reloads its own rows, unused)
       const int cn = min(p + 1, NPASS - 1) * HC;
-      srows.load(static_cast<const T*>(a.Hs) + cs + cn * DV, static_cast<const T*>(ba.dHs) + cs + cn * DV, tid);
+      srows.load(static_cast<const T*>(a.Hs) + cs, static_cast<const T*>(ba.dHs) + cs, cn, tid);
       if ((p & 1) == 1 && p + 1 < NPASS) {   // the next two passes' tiles
         load_pair_regs<T, HC, C>(tKt, hKt, kttile + cn, DK, C, tid);
         load_pair_regs<T, HC, C>(tQ, hQ, qtile + cn, HD, n, tid);

@@ -180,6 +180,16 @@ __device__ __forceinline__ float fast_exp(float x) { return __expf(x); }
 // 2^x on the hardware exponential (a result below the normal range flushes
 // to zero)
 __device__ __forceinline__ float exp2_hw(float x) { return __builtin_amdgcn_exp2f(x); }
+// Element (row, col) of a chunk's saved rows (states and their adjoints: R =
+// d_k rows; E and Z: R = C rows; DV columns).  bf16: in slabs of 32 columns,
+// [DV / 32][R][32], so a scan workgroup's rows are contiguous (its stores and
+// the fragment loads of the chunk kernels touch whole 128-byte lines); fp32:
+// row-major.
+template <typename T, int R, int DV>
+__device__ __forceinline__ constexpr int saved_idx(int row, int col) {
+  return sizeof(T) == 2 ? ((col >> 5) * R + row) * 32 + (col & 31) : row * DV + col;
+}
+
 // natural log on the hardware base-2 logarithm: ln x = ln 2 * log2 x.  x must
 // be a positive normal number (callers clamp); denormal inputs are not
 // rescaled.

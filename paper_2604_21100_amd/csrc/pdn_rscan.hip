@@ -374,11 +374,11 @@ __device__ __forceinline__ void rev_run(const BwdArgs& ba, const RunCtx& x, int 
     constexpr int NP = C / 32;   // pairs of output waves
     const int r0 = 8 * (m >> 2) + 4 * hh + (m & 3);
     const int64_t top = x.c1 - 1, ci = a.ci(x.bh, top);
-    char* hs = static_cast<char*>(ba.dHs) + (ci * DK * a.dv + x.v0) * 2;
-    char* zr = static_cast<char*>(ba.Zr) + (ci * C * a.dv + x.v0) * 2;
+    char* hs = static_cast<char*>(ba.dHs) + (ci * DK * a.dv + x.v0 * DK) * 2;   // (slabs of 32 columns: saved_idx)
+    char* zr = static_cast<char*>(ba.Zr) + (ci * C * a.dv + x.v0 * C) * 2;
     char* dv = static_cast<char*>(ba.dv) + (((x.b * a.T + top * C) * a.H + x.h) * a.dv + x.v0) * 2;
     const uint32_t hv = static_cast<uint32_t>(a.H * a.dv * 2);
-    const uint32_t os = (r0 * a.dv + 8 * g) * 2, ox = (32 * f0 + r0) * hv + 16 * g;
+    const uint32_t os = (r0 * kCols + 8 * g) * 2, ox = (32 * f0 + r0) * hv + 16 * g;
     int64_t left = a.T - top * C;
     lds_sync();
     for (int j = 0; j < cnt; ++j) {
@@ -386,12 +386,12 @@ __device__ __forceinline__ void rev_run(const BwdArgs& ba, const RunCtx& x, int 
 #pragma unroll
         for (int u = 0; u < KK / NP; ++u) {
           const int f = u * NP + f0;
-          *reinterpret_cast<bf16x8*>(hs + os + 64 * f * a.dv) = frag_major_row<KK>(sm + L::oS, f, hh, l);
+          *reinterpret_cast<bf16x8*>(hs + os + 64 * f * kCols) = frag_major_row<KK>(sm + L::oS, f, hh, l);
         }
       }
       lds_sync();
       if (WR) {
-        *reinterpret_cast<bf16x8*>(zr + os + 64 * f0 * a.dv) = frag_major_row<SB>(sm + L::oZ, f0, hh, l);
+        *reinterpret_cast<bf16x8*>(zr + os + 64 * f0 * kCols) = frag_major_row<SB>(sm + L::oZ, f0, hh, l);
         // the chunk's dv rows as a buffer ending with its last valid row
         buf_put16(buf_rsrc(dv, (static_cast<int>(min<int64_t>(C, left)) - 1) * hv + kCols * 2), ox,
                   frag_major_row<SB>(sm + L::oX, f0, hh, l));

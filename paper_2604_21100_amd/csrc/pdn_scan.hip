@@ -461,18 +461,17 @@ __device__ __forceinline__ void keep_store(const FwdArgs& a, int i, const RunCtx
                                            const lds_char* sE, int ow, int l) {
   constexpr int NP = C / 32;   // pairs of output waves
   const int m = l & 15, g = l >> 4, hh = ow & 1;
-  bf16* hs = static_cast<bf16*>(a.Hs) + a.ci(x.bh, i) * static_cast<int64_t>(DK) * a.dv + x.v0;
-  bf16* er = static_cast<bf16*>(a.Er) + a.ci(x.bh, i) * (C * static_cast<int64_t>(a.dv)) + x.v0;
+  // (slabs of 32 columns: saved_idx)
+  bf16* hs = static_cast<bf16*>(a.Hs) + a.ci(x.bh, i) * (DK * static_cast<int64_t>(a.dv)) + x.v0 * DK;
+  bf16* er = static_cast<bf16*>(a.Er) + a.ci(x.bh, i) * (C * static_cast<int64_t>(a.dv)) + x.v0 * C;
   const int r0 = 8 * (m >> 2) + 4 * hh + (m & 3);
 #pragma unroll
   for (int u = 0; u < DK / 32 / NP; ++u) {
     const int f = u * NP + (ow >> 1);
-    *reinterpret_cast<bf16x8*>(at_bytes(hs, static_cast<uint32_t>((32 * f + r0) * a.dv + 8 * g) * 2u)) =
-        frag_major_row<DK / 32>(sS, f, hh, l);
+    *reinterpret_cast<bf16x8*>(hs + (32 * f + r0) * kCols + 8 * g) = frag_major_row<DK / 32>(sS, f, hh, l);
   }
   const int f = ow >> 1;
-  *reinterpret_cast<bf16x8*>(at_bytes(er, static_cast<uint32_t>((32 * f + r0) * a.dv + 8 * g) * 2u)) =
-      frag_major_row<C / 32>(sE, f, hh, l);
+  *reinterpret_cast<bf16x8*>(er + (32 * f + r0) * kCols + 8 * g) = frag_major_row<C / 32>(sE, f, hh, l);
 }
 
 template <int DK, int GATE, bool SAVE, bool OUT, bool LA, int C, bool PSCAN>
