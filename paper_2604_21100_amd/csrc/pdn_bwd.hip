@@ -642,8 +642,9 @@ __device__ __forceinline__ void buf_store16(__amdgpu_buffer_rsrc_t r, uint32_t o
 // staging (the wave reads back only what it wrote: no barrier needed):
 // 16-byte stores, a fixed count per lane.  dq is the chunk's rows of the
 // caller's [B,T,H,dk] tensor as a buffer ending with its last valid row, so
-// rows past the sequence end are dropped; dKm / dKt are padded workspace.
-template <typename T, int HC, int LDO, int DK>
+// rows past the sequence end are dropped; dKm / dKt are padded workspace
+// (saved_idx: a pass's 32 columns are whole lines there).
+template <typename T, int HC, int LDO, int DK, int C>
 __device__ __forceinline__ void p12_flush_rows(const T* so, __amdgpu_buffer_rsrc_t dqr, int64_t HD,
                                                int c0, T* dKm, T* dKt, int w, int l) {
   constexpr int VEC = 16 / sizeof(T), SPR = HC / VEC;
@@ -656,8 +657,9 @@ __device__ __forceinline__ void p12_flush_rows(const T* so, __amdgpu_buffer_rsrc
     const float4 vk = *reinterpret_cast<const float4*>(so + (16 + rr) * LDO + sgc);
     const float4 vt = *reinterpret_cast<const float4*>(so + (32 + rr) * LDO + sgc);
     buf_store16(dqr, static_cast<uint32_t>((r * HD + c0 + sgc) * static_cast<int64_t>(sizeof(T))), vq);
-    *reinterpret_cast<float4*>(dKm + r * DK + c0 + sgc) = vk;
-    *reinterpret_cast<float4*>(dKt + r * DK + c0 + sgc) = vt;
+    const int o = saved_idx<T, C, DK>(r, c0 + sgc);
+    *reinterpret_cast<float4*>(dKm + o) = vk;
+    *reinterpret_cast<float4*>(dKt + o) = vt;
   }
 }
 
@@ -989,7 +991,7 @@ __global__ __launch_bounds__(256, 2) void p12_chunk_grads(BwdArgs ba) {
       st4<T>(so + 16 * LDO, ak[0], ak[1], ak[2], ak[3]);
       st4<T>(so + 32 * LDO, at[0], at[1], at[2], at[3]);
     }
-    if (rows) p12_flush_rows<T, HC, LDO, DK>(sOut + w * 3 * 16 * LDO, dqr, HD, c0, dKm, dKt, w, l);
+    if (rows) p12_flush_rows<T, HC, LDO, DK, C>(sOut + w * 3 * 16 * LDO, dqr, HD, c0, dKm, dKt, w, l);
   }
 #pragma unroll
   for (int off = 16; off < 64; off <<= 1) {
@@ -1359,7 +1361,7 @@ __global__ __launch_bounds__(256, 2) void p12c_chunk_grads(BwdArgs ba) {
         so[(32 + 4 * lg + ii) * LDO + c] = from_f<T>(ot[ii]);
       }
     }
-    if (rows) p12_flush_rows<T, HC, LDO, DK>(sOut + w * 3 * 16 * LDO, dqr, HD, c0, dKm, dKt, w, l);
+    if (rows) p12_flush_rows<T, HC, LDO, DK, C>(sOut + w * 3 * 16 * LDO, dqr, HD, c0, dKm, dKt, w, l);
     __syncthreads();
     {
       // dg_j = sum_{r >= j} dG_r + the last-row term, per channel: C / 8
@@ -1605,7 +1607,7 @@ __global__ __launch_bounds__(64 * (C / PCG)) void pc_chunk(BwdArgs ba) {
 #pragma unroll
   for (int j = 0; j < PCG; ++j) {
     const uint32_t rr = static_cast<uint32_t>(min(s0 + j, n - 1));
-    const uint32_t ow = static_cast<uint32_t>((s0 + j) * DK) * E + lo;
+    const uint32_t ow = static_cast<uint32_t>(saved_idx<T, C, DK>(s0 + j, c0)) * E;
     kr[j] = *reinterpret_cast<const Pt*>(at_bytes(kb, rr * kstb + lo));
     gr[j] = *reinterpret_cast<const Pt*>(at_bytes(gb, ow));
   }
@@ -1728,9 +1730,10 @@ __global__ __launch_bounds__(64 * (C / PCG)) void pc_chunk(BwdArgs ba) {
   // (the lane offset is pinned here too, or the compiler forms the sixteen
   // addresses before the forward recurrence and holds them through it; the
   // rows are steps of one pointer, so they become immediate offsets)
-  const Pt* mrow = reinterpret_cast<const Pt*>(at_bytes(mb + s0 * DK, pc_pin(lo)));
+  const Pt* mrow = reinterpret_cast<const Pt*>(at_bytes(mb, pc_pin(static_cast<uint32_t>(saved_idx<T, C, DK>(s0, c0)) * E)));
+  constexpr int kRowStep = saved_idx<T, C, DK>(1, 0) / CPL;
 #pragma unroll
-  for (int j = 0; j < PCG; ++j) mr[j] = mrow[j * (DK / CPL)];
+  for (int j = 0; j < PCG; ++j) mr[j] = mrow[j * kRowStep];
   const float xB = exp2_hw(-nlx2);   // B where A <= 0: x
   float sb[PCG], sg[PCG];
   float muPart = 0.f;
@@ -1857,7 +1860,10 @@ __global__ __launch_bounds__(256) void combine_dk(BwdArgs ba) {
   const int c = static_cast<int>(idx % DK);
   const int64_t tok = idx / DK;
   const int64_t h = tok % a.H, t = (tok / a.H) % a.T, b = tok / (a.H * a.T);
-  const int64_t w = (a.ci(b * a.H + h, t / a.chunk) * a.chunk + t % a.chunk) * DK + c;
+  // (saved_idx at either chunk length)
+  const int r = static_cast<int>(t % a.chunk);
+  const int64_t w = a.ci(b * a.H + h, t / a.chunk) * a.chunk * DK +
+                    (a.chunk == 32 ? saved_idx<T, 32, DK>(r, c) : saved_idx<T, 64, DK>(r, c));
   const float km = to_f(static_cast<const T*>(ba.dKm)[w]), kt = to_f(static_cast<const T*>(ba.dKt)[w]);
   if (a.precond == kIdentity) {
     static_cast<T*>(ba.dk)[idx] = from_f<T>(km + kt);

@@ -181,9 +181,10 @@ __device__ __forceinline__ float fast_exp(float x) { return __expf(x); }
 // to zero)
 __device__ __forceinline__ float exp2_hw(float x) { return __builtin_amdgcn_exp2f(x); }
 // Element (row, col) of a chunk's saved rows (states and their adjoints: R =
-// d_k rows; E and Z: R = C rows; DV columns).  bf16: in slabs of 32 columns,
-// [DV / 32][R][32], so a scan workgroup's rows are contiguous (its stores and
-// the fragment loads of the chunk kernels touch whole 128-byte lines); fp32:
+// d_k rows; E, Z and the key gradients: R = C rows; DV columns).  bf16: in slabs of 32 columns,
+// [DV / 32][R][32], so a scan workgroup's rows, and those of a 32-column pass of
+// the chunk kernels, are contiguous (stores and fragment loads touch whole
+// 128-byte lines); fp32:
 // row-major.
 template <typename T, int R, int DV>
 __device__ __forceinline__ constexpr int saved_idx(int row, int col) {

@@ -66,7 +66,7 @@ struct FwdArgs {
   void* KL;       // [BH, Tpad, dk] io   per-channel gate: Lam o K
   // backward only (NULL in the forward): forward intermediates kept for the
   // adjoint kernels.  lam_r = exp(G_r), w_r = exp(G_{C-1} - G_r).
-  // (per-chunk tensors are indexed by ci(); bf16 Hs, Er, dHs, Zr: saved_idx)
+  // (per-chunk tensors are indexed by ci(); bf16 Hs, Er, dHs, Zr, dKt, dKm: saved_idx)
   void* Hs;       // [BH, NT, dk, dv] io  chunk-start states S^T
   void* Er;       // [BH, Tpad, dv] io    E = T X rows
   // (fp32 only, the transposed operands its reverse scan reads:)
