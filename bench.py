@@ -88,23 +88,36 @@ def algorithmic_per_token_head(spec, train=False, precond="squash"):
              + sh + ah)                                        # dS0, dA0
     # per stage: (flop, method bytes, design bytes)
     pre = (3 * dk, e * dk + pb + 2 * ah, e * dk + pb + 4 * dk / C)
+    # bf16 scans read row-major operands and, without the per-channel gate,
+    # form P themselves where their slabs fill the chip and runs are long
+    # (the library's scan_forms_p): the preparation then reads no queries
+    rows, chan = e == 2, spec.gate == "channel"
+    forms_p = (rows and not chan and precond != "atq"
+               and spec.B * spec.H * dv // 32 >= 256 and -(-T // C) >= 32)
+    pc = 0 if forms_p else e * C          # P written by the preparation
+    gw = 4 * dk / C if chan else gb       # gate prefix (chunk-end row)
     # k2: reads q, k, beta, g, betaP, gP and the chunk-start A; writes the
-    # decayed write keys (dk), T and P (C each) and the gate prefix
-    prep_m = e * 2 * dk + 4 + gb + pb + xk
+    # write keys (dk), the inverse (C), P (C) and the gate prefix; per-channel
+    # gate: also the decayed query and key rows
+    prep_m = e * (1 if forms_p else 2) * dk + 4 + gb + pb + xk
     prep = (4 * C * dk + C * C / 3.0, prep_m,
-            prep_m + 4 * dk / C + e * (dk + 2 * C) + gb)
-    # k2 (backward mode): also P^T and M^T (C each) and the write-key,
-    # decayed write-key, decayed query and key rows (dk each)
-    prep_b = (prep[0], prep_m, prep[2] + 2 * e * C + 4 * e * dk)
-    # k3: reads q, k, v; writes o and S_T (reads T, P, decayed write keys and
-    # the gate prefix from the workspace)
+            prep_m + 4 * dk / C + e * (dk + C) + pc + gw + (2 * e * dk if chan else 0))
+    # k2 (backward mode): bf16, per-channel gate: also the plain write-key
+    # rows; fp32: also P^T and M^T (C each) and the write-key, decayed query
+    # and key rows (dk each)
+    prep_b = (prep[0], prep_m, prep[2] + ((e * dk if chan else 0) if rows
+                                          else 2 * e * C + 3 * e * dk))
+    # k3: reads q, k, v; writes o and S_T (reads the inverse, P, the write
+    # keys and the gate prefix from the workspace)
     scan_m = e * (2 * dk + dv) + e * dv + s0 + sh
     scan = (6 * dk * dv + 4 * C * dv, scan_m,
-            e * (2 * dk + dv) + e * (2 * C + dk) + gb + e * dv + s0 + sh)
-    # k3 (saving, no output): reads k, v, T, decayed write keys, gate prefix;
-    # writes the chunk-start states and the E rows
+            e * (2 * dk + dv) + e * (C + dk) + pc + gw + e * dv + s0 + sh)
+    # k3 (saving, no output): reads k, v, the inverse, the write keys and the
+    # gate prefix (forming P: q too); writes the chunk-start states, the E
+    # rows (and P)
     save = (4 * dk * dv + 2 * C * dv, e * (dk + dv) + s0,
-            e * (dk + dv) + e * (C + dk) + gb + st + e * dv + s0)
+            e * (dk + dv) + e * (C + dk) + gw + st + e * dv + s0
+            + (e * (dk + C) if forms_p else 0))
     if precond == "atq":
         # linear attention read through the preconditioned query: no
         # interaction matrix or solve; the prep kernel also writes the
@@ -116,14 +129,14 @@ def algorithmic_per_token_head(spec, train=False, precond="squash"):
         "precond": pre,
         "chunk_prep": prep_b if train else prep,
         # training forward: the output, the saved states and E rows
-        "chunk_scan": ((scan[0], scan[1], scan[2] + st + e * dv) if train
-                       else scan),
+        "chunk_scan": ((scan[0], scan[1], scan[2] + st + e * dv
+                        + (e * C if forms_p else 0)) if train else scan),
         "bwd_precond_recompute": pre,
         "bwd_chunk_prep": prep_b,
         "bwd_state_save_scan": save,
-        # r1: reads dO and beta, writes dv and dS0 (method); also reads P^T,
-        # M^T, the write keys, (lam Q)^T, -(lam K)^T and writes the state
-        # adjoints and the Z rows
+        # r1: reads dO and beta, writes dv and dS0 (method); also reads P,
+        # the inverse, the write keys, q and k (or their decayed rows) and
+        # writes the state adjoints and the Z rows
         "bwd_state_adjoint_scan": (4 * C * dv + 6 * dk * dv,
                                    2 * e * dv + 4 + sh,
                                    2 * e * C + 3 * e * dk + e * dv + 4
@@ -145,6 +158,7 @@ def algorithmic_per_token_head(spec, train=False, precond="squash"):
 
 SCAN_STAGES = ("chunk_scan", "bwd_state_save_scan", "bwd_state_adjoint_scan")
 
+# (stage names; the bf16 scans are the kernels fwd_scan and rev_scan)
 KERNELS = {
     "precond": "k1_precond_summary+k1_precond_carry",
     "chunk_prep": "k2_chunk_prep",
