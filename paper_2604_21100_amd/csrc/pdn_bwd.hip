@@ -27,8 +27,8 @@
 // plus the gate terms (gradients of lam, w, lam_C and Gam, reverse-summed
 // over the chunk) and the preconditioner's reverse scan.
 //
-//   r1_state_adjoint   sequential over chunks (reverse): dS^T carry, dE, Z,
-//                      dX (= dv)
+//   r1_state_adjoint   (fp32; bf16: rev_scan in pdn_rscan.hip) sequential over
+//                      chunks (reverse): dS^T carry, dE, Z, dX (= dv)
 //   p12_chunk_grads    per chunk: the C x C adjoints (dSqk, dSkk), dq, the
 //                      read- and write-key gradients, dbeta, dg
 //   p12c_chunk_grads   the same for the per-channel gate (decay inside the

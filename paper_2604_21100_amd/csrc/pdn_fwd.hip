@@ -12,10 +12,11 @@
 //                       on MFMA, the unit-lower inverse T = (I+At)^{-1}Diag(beta)
 //                       (Eq. T_two_key) and the decayed write keys for the
 //                       state update
-//   k3_chunk_scan       per (head, 32-column value slab): the sequential
-//                       inter-chunk state scan with the chunk output fused in
-//                       (Eq. chunkwise_atk_form; decayed forms of App. D),
-//                       using E = U - W S^T = T (V - (Lam*K) S^T)
+//   k3_chunk_scan       (fp32; bf16: fwd_scan in pdn_scan.hip) per (head,
+//                       32-column value slab): the sequential inter-chunk
+//                       state scan with the chunk output fused in (Eq.
+//                       chunkwise_atk_form; decayed forms of App. D), using
+//                       E = U - W S^T = T (V - (Lam*K) S^T)
 #include <mutex>
 
 #include "pdn_device.hpp"
@@ -186,9 +187,17 @@ struct K2Smem {
   static constexpr size_t kTotal = kR1 + kR2 + kR3 + kGc + kYs + kScal + kTail;
 };
 
-// BWD: also write the operand layouts the backward kernels read (P^T, M^T,
-// write-key rows, write-key rows decayed to the chunk end, (Lam o Q)^T and
-// -(Lam o K)^T; Lam the scalar or per-channel in-chunk decay).
+// BWD: also write what only the backward kernels read: in bf16 the plain
+// write-key rows of the per-channel gate; in fp32 P^T, M^T, write-key rows,
+// write-key rows decayed to the chunk end, (Lam o Q)^T and -(Lam o K)^T (Lam
+// the scalar or per-channel in-chunk decay).
+//
+// What bounds it: a block's chain of phases (loads, two walks of the
+// preconditioner, the C x C product, the solve), overlapped by the blocks that
+// share a CU.  1B layer (B = 4, T = 4096, H = 16, d = 128, scalar gate): 101 us
+// with three blocks per CU, the queries read and P written; 81 us with PSCAN.
+// Of the 101, timing copies put 15 in the solve, 26 in the stores, 8 in the
+// squash and 8 in the MFMA.
 template <typename T, int DK, int GATE, int PREC, bool BWD, int C, bool PSCAN>
 __global__ __launch_bounds__(256, PSCAN ? 4 : 3) void k2_chunk_prep(FwdArgs a) {
   using SM = K2Smem<T, DK, GATE, PREC, C, PSCAN>;
