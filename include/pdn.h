@@ -31,6 +31,10 @@
  *     paper's S), i.e. element (b, h, i, j) is S[j][i].
  *   - q, k, v, o, ktilde and their gradients use the problem's io dtype
  *     (IEEE fp32 or bfloat16); every other tensor is fp32.
+ *   - Byte offsets inside a chunk of q, k, v, o and their gradients are 32-bit:
+ *     (min(T, chunk) - 1) * H * max(dk, dv) * element size must stay below
+ *     2^32 - 1024 (in bf16 at d = 128 and T >= chunk = 64: H up to 266304).
+ *     Nothing checks it.
  *   - Calls are asynchronous on the given HIP stream (a hipStream_t passed as
  *     void*; NULL = the null stream).  Inputs, outputs and workspace must stay
  *     valid until the stream work completes.

@@ -656,7 +656,7 @@ __device__ __forceinline__ void p12_flush_rows(const T* so, __amdgpu_buffer_rsrc
     const float4 vq = *reinterpret_cast<const float4*>(so + rr * LDO + sgc);
     const float4 vk = *reinterpret_cast<const float4*>(so + (16 + rr) * LDO + sgc);
     const float4 vt = *reinterpret_cast<const float4*>(so + (32 + rr) * LDO + sgc);
-    buf_store16(dqr, static_cast<uint32_t>((r * HD + c0 + sgc) * static_cast<int64_t>(sizeof(T))), vq);
+    buf_store16(dqr, row_off(r, static_cast<uint32_t>(HD * static_cast<int64_t>(sizeof(T))), (c0 + sgc) * sizeof(T)), vq);
     const int o = saved_idx<T, C, DK>(r, c0 + sgc);
     *reinterpret_cast<float4*>(dKm + o) = vk;
     *reinterpret_cast<float4*>(dKt + o) = vt;
@@ -916,7 +916,7 @@ __global__ __launch_bounds__(256, 2) void p12_chunk_grads(BwdArgs ba) {
   float red = 0.f;
   T* dq = static_cast<T*>(ba.dq) + (b * a.T + t0) * HD + h * DK;
   // the chunk's dq rows as a raw buffer ending with row n - 1: a row r >= n
-  // starts at r HD >= (n - 1) HD + DK elements, past the range
+  // starts at r HD >= (n - 1) HD + DK elements, past the range (row_off)
   const __amdgpu_buffer_rsrc_t dqr = __builtin_amdgcn_make_buffer_rsrc(
       dq, 0, static_cast<int>(((n - 1) * HD + DK) * static_cast<int64_t>(sizeof(T))), kBufWord3);
   T* dKm = static_cast<T*>(ba.dKm) + rk;
@@ -1207,7 +1207,7 @@ __global__ __launch_bounds__(256, 2) void p12c_chunk_grads(BwdArgs ba) {
   float pdb[4] = {0.f, 0.f, 0.f, 0.f};
   T* dq = static_cast<T*>(ba.dq) + (b * a.T + t0) * HD + h * DK;
   // the chunk's dq rows as a raw buffer ending with row n - 1: a row r >= n
-  // starts at r HD >= (n - 1) HD + DK elements, past the range
+  // starts at r HD >= (n - 1) HD + DK elements, past the range (row_off)
   const __amdgpu_buffer_rsrc_t dqr = __builtin_amdgcn_make_buffer_rsrc(
       dq, 0, static_cast<int>(((n - 1) * HD + DK) * static_cast<int64_t>(sizeof(T))), kBufWord3);
   T* dKm = static_cast<T*>(ba.dKm) + rk;
@@ -1739,7 +1739,7 @@ __global__ __launch_bounds__(64 * (C / PCG)) void pc_chunk(BwdArgs ba) {
   float muPart = 0.f;
   T* dkb = static_cast<T*>(ba.dk) + ((b * a.T + t0) * a.H + h) * DK;
   // this (b, h, chunk)'s dk rows as a raw buffer ending with row n - 1:
-  // a row r >= n starts at r kstb >= (n - 1) kstb + DK E, past the range
+  // a row r >= n starts at r kstb >= (n - 1) kstb + DK E, past the range (row_off)
   const __amdgpu_buffer_rsrc_t dkr = __builtin_amdgcn_make_buffer_rsrc(
       dkb, 0, static_cast<int>((n - 1) * kstb + DK * E), kBufWord3);
   Pk Acur = sA[w][PCG - 1][l];
@@ -1766,7 +1766,7 @@ __global__ __launch_bounds__(64 * (C / PCG)) void pc_chunk(BwdArgs ba) {
       sg[j] = q == 0 ? D[q] * Aprev.x[q] : fmaf(D[q], Aprev.x[q], sg[j]);
     }
     Acur = Aprev;
-    pc_store(dkr, static_cast<uint32_t>(s0 + j) * kstb + lo, pc_pack<T, CPL>(o));
+    pc_store(dkr, row_off(s0 + j, kstb, lo), pc_pack<T, CPL>(o));
   }
   // lane 4 j carries token s0 + j's sums
   const int jl = l >> 2;

@@ -170,6 +170,19 @@ __device__ __forceinline__ void st_tile_t(T* out, int ld, const floatx4& acc, in
 // chips: a 32-bit data format, which untyped accesses need to be non-zero.
 constexpr int kBufWord3 = 0x00020000;
 
+// A chunk's token rows are seen through a raw buffer that ends with its last
+// valid row, so accesses to the rows past it are dropped by the range check.
+// Their offsets must then not wrap: with hundreds of thousands of heads
+// (a row stride of H d elements) r * stride passes 2^32 while the valid rows'
+// offsets still fit, and a wrapped one would fall on another row.  Such an
+// offset stays at kPastRange, past every range (256 bytes short of 2^32, so
+// that a column offset added to it does not wrap either).
+constexpr uint32_t kPastRange = 0xffffff00u;
+__device__ __forceinline__ uint32_t row_off(uint32_t r, uint32_t stride, uint32_t x) {
+  const uint64_t o = static_cast<uint64_t>(r) * stride + x;
+  return o < kPastRange ? static_cast<uint32_t>(o) : kPastRange;
+}
+
 constexpr float kLn2 = 0.6931471805599453f;
 constexpr float kLog2e = 1.4426950408889634f;
 // v where ok, else zeros (per component, so the value stays in registers)

@@ -378,7 +378,7 @@ __device__ __forceinline__ void rev_run(const BwdArgs& ba, const RunCtx& x, int 
     char* zr = static_cast<char*>(ba.Zr) + (ci * C * a.dv + x.v0 * C) * 2;
     char* dv = static_cast<char*>(ba.dv) + (((x.b * a.T + top * C) * a.H + x.h) * a.dv + x.v0) * 2;
     const uint32_t hv = static_cast<uint32_t>(a.H * a.dv * 2);
-    const uint32_t os = (r0 * kCols + 8 * g) * 2, ox = (32 * f0 + r0) * hv + 16 * g;
+    const uint32_t os = (r0 * kCols + 8 * g) * 2, ox = row_off(32 * f0 + r0, hv, 16 * g);
     int64_t left = a.T - top * C;
     lds_sync();
     for (int j = 0; j < cnt; ++j) {

@@ -331,16 +331,17 @@ __device__ __forceinline__ bf16x8 buf_get16(__amdgpu_buffer_rsrc_t r, uint32_t o
 template <int DK, int GATE, int C, bool LA>
 struct OutLanes {
   static constexpr bool WS = GATE == kGateChannel || LA;
-  uint32_t q, qrow, p, g, o;
+  uint32_t q, q1, p, g, o;   // q, q1: the pair's two query rows
   bool odd;
   __device__ __forceinline__ OutLanes(const ChunkCursor& c, int ow, int l) {
     const int m = l & 15, lg = l >> 4, r = 16 * ow + m;
     odd = m & 1;
-    qrow = WS ? DK * 2 : c.hd;
-    q = (r & ~1) * qrow + 64 * (m & 1) + 16 * lg;
+    const uint32_t qrow = WS ? DK * 2 : c.hd, qc = 64 * (m & 1) + 16 * lg;
+    q = row_off(r & ~1, qrow, qc);
+    q1 = row_off(r | 1, qrow, qc);
     p = C == 64 ? (r & ~1) * (C * 2) + 64 * (m & 1) + 16 * lg : r * (C * 2) + 16 * lg;
     g = (12 + r / (C / 4)) * (2 * C) + C + (r % (C / 4)) * 4;   // G_r, among the scalars in M
-    o = r * c.hv + 16 * lg;
+    o = row_off(r, c.hv, 16 * lg);
   }
 };
 
@@ -357,7 +358,7 @@ __device__ __forceinline__ void out_load(OutRows<DK, GATE, C, LA>& f, ChunkCurso
 #pragma unroll
   for (int kk = 0; kk < KK; kk += 2) {
     f.q[kk] = buf_get16(rq, o.q + 64 * kk);
-    f.q[kk + 1] = buf_get16(rq, o.q + 64 * kk + o.qrow);
+    f.q[kk + 1] = buf_get16(rq, o.q1 + 64 * kk);
   }
   if (!PSCAN)
 #pragma unroll

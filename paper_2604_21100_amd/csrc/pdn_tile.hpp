@@ -121,7 +121,7 @@ template <int NCH>
 __device__ __forceinline__ uint32_t unit_src(int u, int l, uint32_t row_bytes) {
   const int r = u * (64 / NCH) + l / NCH;
   const int ch = (tile_off<NCH>(r, l % NCH) / 16) % NCH;   // the chunk at position l % NCH of its row
-  return static_cast<uint32_t>(r) * row_bytes + 16u * ch;
+  return row_off(static_cast<uint32_t>(r), row_bytes, 16u * ch);
 }
 __device__ __forceinline__ void unit_copy(__amdgpu_buffer_rsrc_t r, uint32_t off, lds_char* dst) {
   __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)dst, 16, static_cast<int>(off),
