@@ -641,11 +641,11 @@ __device__ __forceinline__ void buf_store16(__amdgpu_buffer_rsrc_t r, uint32_t o
 // One wave's 16 output rows x HC columns of dq, dK and dKt, from its LDS
 // staging (the wave reads back only what it wrote: no barrier needed):
 // 16-byte stores, a fixed count per lane.  dq is the chunk's rows of the
-// caller's [B,T,H,dk] tensor as a buffer ending with its last valid row, so
-// rows past the sequence end are dropped; dKm / dKt are padded workspace
+// caller's [B,T,H,dk] tensor as a buffer, the n valid ones: the rows past the
+// sequence end are dropped (kPastRange); dKm / dKt are padded workspace
 // (saved_idx: a pass's 32 columns are whole lines there).
 template <typename T, int HC, int LDO, int DK, int C>
-__device__ __forceinline__ void p12_flush_rows(const T* so, __amdgpu_buffer_rsrc_t dqr, int64_t HD,
+__device__ __forceinline__ void p12_flush_rows(const T* so, __amdgpu_buffer_rsrc_t dqr, int64_t HD, int n,
                                                int c0, T* dKm, T* dKt, int w, int l) {
   constexpr int VEC = 16 / sizeof(T), SPR = HC / VEC;
   static_assert(16 * SPR % 64 == 0, "whole rounds of the wave");
@@ -656,7 +656,8 @@ __device__ __forceinline__ void p12_flush_rows(const T* so, __amdgpu_buffer_rsrc
     const float4 vq = *reinterpret_cast<const float4*>(so + rr * LDO + sgc);
     const float4 vk = *reinterpret_cast<const float4*>(so + (16 + rr) * LDO + sgc);
     const float4 vt = *reinterpret_cast<const float4*>(so + (32 + rr) * LDO + sgc);
-    buf_store16(dqr, row_off(r, static_cast<uint32_t>(HD * static_cast<int64_t>(sizeof(T))), (c0 + sgc) * sizeof(T)), vq);
+    const uint32_t oq = static_cast<uint32_t>((r * HD + c0 + sgc) * static_cast<int64_t>(sizeof(T)));
+    buf_store16(dqr, r < n ? oq : kPastRange, vq);
     const int o = saved_idx<T, C, DK>(r, c0 + sgc);
     *reinterpret_cast<float4*>(dKm + o) = vk;
     *reinterpret_cast<float4*>(dKt + o) = vt;
@@ -915,8 +916,7 @@ __global__ __launch_bounds__(256, 2) void p12_chunk_grads(BwdArgs ba) {
   float pq = 0.f, pk = 0.f, pw = 0.f;
   float red = 0.f;
   T* dq = static_cast<T*>(ba.dq) + (b * a.T + t0) * HD + h * DK;
-  // the chunk's dq rows as a raw buffer ending with row n - 1: a row r >= n
-  // starts at r HD >= (n - 1) HD + DK elements, past the range (row_off)
+  // the chunk's dq rows as a raw buffer ending with row n - 1
   const __amdgpu_buffer_rsrc_t dqr = __builtin_amdgcn_make_buffer_rsrc(
       dq, 0, static_cast<int>(((n - 1) * HD + DK) * static_cast<int64_t>(sizeof(T))), kBufWord3);
   T* dKm = static_cast<T*>(ba.dKm) + rk;
@@ -991,7 +991,7 @@ __global__ __launch_bounds__(256, 2) void p12_chunk_grads(BwdArgs ba) {
       st4<T>(so + 16 * LDO, ak[0], ak[1], ak[2], ak[3]);
       st4<T>(so + 32 * LDO, at[0], at[1], at[2], at[3]);
     }
-    if (rows) p12_flush_rows<T, HC, LDO, DK, C>(sOut + w * 3 * 16 * LDO, dqr, HD, c0, dKm, dKt, w, l);
+    if (rows) p12_flush_rows<T, HC, LDO, DK, C>(sOut + w * 3 * 16 * LDO, dqr, HD, n, c0, dKm, dKt, w, l);
   }
 #pragma unroll
   for (int off = 16; off < 64; off <<= 1) {
@@ -1206,8 +1206,7 @@ __global__ __launch_bounds__(256, 2) void p12c_chunk_grads(BwdArgs ba) {
   // ---- phase B
   float pdb[4] = {0.f, 0.f, 0.f, 0.f};
   T* dq = static_cast<T*>(ba.dq) + (b * a.T + t0) * HD + h * DK;
-  // the chunk's dq rows as a raw buffer ending with row n - 1: a row r >= n
-  // starts at r HD >= (n - 1) HD + DK elements, past the range (row_off)
+  // the chunk's dq rows as a raw buffer ending with row n - 1
   const __amdgpu_buffer_rsrc_t dqr = __builtin_amdgcn_make_buffer_rsrc(
       dq, 0, static_cast<int>(((n - 1) * HD + DK) * static_cast<int64_t>(sizeof(T))), kBufWord3);
   T* dKm = static_cast<T*>(ba.dKm) + rk;
@@ -1361,7 +1360,7 @@ __global__ __launch_bounds__(256, 2) void p12c_chunk_grads(BwdArgs ba) {
         so[(32 + 4 * lg + ii) * LDO + c] = from_f<T>(ot[ii]);
       }
     }
-    if (rows) p12_flush_rows<T, HC, LDO, DK, C>(sOut + w * 3 * 16 * LDO, dqr, HD, c0, dKm, dKt, w, l);
+    if (rows) p12_flush_rows<T, HC, LDO, DK, C>(sOut + w * 3 * 16 * LDO, dqr, HD, n, c0, dKm, dKt, w, l);
     __syncthreads();
     {
       // dg_j = sum_{r >= j} dG_r + the last-row term, per channel: C / 8
@@ -1738,8 +1737,8 @@ __global__ __launch_bounds__(64 * (C / PCG)) void pc_chunk(BwdArgs ba) {
   float sb[PCG], sg[PCG];
   float muPart = 0.f;
   T* dkb = static_cast<T*>(ba.dk) + ((b * a.T + t0) * a.H + h) * DK;
-  // this (b, h, chunk)'s dk rows as a raw buffer ending with row n - 1:
-  // a row r >= n starts at r kstb >= (n - 1) kstb + DK E, past the range (row_off)
+  // this (b, h, chunk)'s dk rows as a raw buffer ending with row n - 1; the
+  // rows past it are dropped (kPastRange)
   const __amdgpu_buffer_rsrc_t dkr = __builtin_amdgcn_make_buffer_rsrc(
       dkb, 0, static_cast<int>((n - 1) * kstb + DK * E), kBufWord3);
   Pk Acur = sA[w][PCG - 1][l];
@@ -1766,7 +1765,7 @@ __global__ __launch_bounds__(64 * (C / PCG)) void pc_chunk(BwdArgs ba) {
       sg[j] = q == 0 ? D[q] * Aprev.x[q] : fmaf(D[q], Aprev.x[q], sg[j]);
     }
     Acur = Aprev;
-    pc_store(dkr, row_off(s0 + j, kstb, lo), pc_pack<T, CPL>(o));
+    pc_store(dkr, (s0 + j < n ? static_cast<uint32_t>(s0 + j) * kstb : kPastRange) + lo, pc_pack<T, CPL>(o));
   }
   // lane 4 j carries token s0 + j's sums
   const int jl = l >> 2;
