@@ -443,11 +443,9 @@ __global__ __launch_bounds__(scan_threads(C), 2) void rev_scan(BwdArgs ba) {
   const int nrole = a.seg_phase == 0 ? nslab
                   : a.seg_phase == 1 ? nslab + (S - 2) * (nslab + npslab)
                                      : (S - 1) * nslab;
-  const int64_t bid = blockIdx.x;
-  const int64_t j8 = bid >> 3;
-  const int role = static_cast<int>(j8 % nrole);
+  int role;
   RunCtx x;
-  x.bh = (j8 / nrole) * 8 + (bid & 7);
+  x.bh = scan_head(nrole, &role);
   if (x.bh >= a.BH) return;
   x.b = x.bh / a.H;
   x.h = x.bh % a.H;
@@ -478,8 +476,7 @@ hipError_t launch_typed(const BwdArgs& ba, hipStream_t s) {
   const int nslab = a.dv / kCols, npslab = DK / kCols;
   auto launch = [&](int phase, int nrole) {
     a.seg_phase = phase;
-    hipLaunchKernelGGL((rev_scan<DK, GATE, C>), dim3(static_cast<unsigned>(((a.BH + 7) / 8) * 8 * nrole)),
-                       dim3(scan_threads(C)), 0, s, b);
+    hipLaunchKernelGGL((rev_scan<DK, GATE, C>), scan_grid(a.BH, nrole), dim3(scan_threads(C)), 0, s, b);
     return hipGetLastError();
   };
   if (a.seg_cnt < 3) return launch(0, nslab);

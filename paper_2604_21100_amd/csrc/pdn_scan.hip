@@ -638,11 +638,9 @@ __global__ __launch_bounds__(scan_threads(C), 2) void fwd_scan(FwdArgs a) {
   const int nrole = a.seg_phase == 0 ? nslab
                   : a.seg_phase == 1 ? nslab + (S - 2) * (nslab + npslab)
                                      : (S - 1) * nslab;
-  const int64_t bid = blockIdx.x;
-  const int64_t j8 = bid >> 3;
-  const int role = static_cast<int>(j8 % nrole);
+  int role;
   RunCtx x;
-  x.bh = (j8 / nrole) * 8 + (bid & 7);
+  x.bh = scan_head(nrole, &role);
   if (x.bh >= a.BH) return;
   x.b = x.bh / a.H;
   x.h = x.bh % a.H;
@@ -672,21 +670,22 @@ template <int DK, int GATE, bool SAVE, bool OUT, bool LA, int C, bool PSCAN>
 hipError_t launch_typed(const FwdArgs& a0, hipStream_t s) {
   FwdArgs a = a0;
   const int nslab = a.dv / kCols, npslab = DK / kCols;
-  auto grid = [&](int nrole) { return dim3(static_cast<unsigned>(((a.BH + 7) / 8) * 8 * nrole)); };
   if (a.seg_cnt < 3) {
     a.seg_phase = 0;
-    hipLaunchKernelGGL((fwd_scan<DK, GATE, SAVE, OUT, LA, C, PSCAN>), grid(nslab), dim3(scan_threads(C)), 0, s, a);
+    hipLaunchKernelGGL((fwd_scan<DK, GATE, SAVE, OUT, LA, C, PSCAN>), scan_grid(a.BH, nslab), dim3(scan_threads(C)),
+                       0, s, a);
     return hipGetLastError();
   }
   const int S = a.seg_cnt;
   a.seg_phase = 1;
-  hipLaunchKernelGGL((fwd_scan<DK, GATE, SAVE, OUT, LA, C, PSCAN>), grid(nslab + (S - 2) * (nslab + npslab)), dim3(scan_threads(C)), 0, s,
-                     a);
+  hipLaunchKernelGGL((fwd_scan<DK, GATE, SAVE, OUT, LA, C, PSCAN>),
+                     scan_grid(a.BH, nslab + (S - 2) * (nslab + npslab)), dim3(scan_threads(C)), 0, s, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if ((e = launch_seg_compose(a, false, s)) != hipSuccess) return e;
   a.seg_phase = 3;
-  hipLaunchKernelGGL((fwd_scan<DK, GATE, SAVE, OUT, LA, C, PSCAN>), grid((S - 1) * nslab), dim3(scan_threads(C)), 0, s, a);
+  hipLaunchKernelGGL((fwd_scan<DK, GATE, SAVE, OUT, LA, C, PSCAN>), scan_grid(a.BH, (S - 1) * nslab),
+                     dim3(scan_threads(C)), 0, s, a);
   return hipGetLastError();
 }
 

@@ -96,6 +96,23 @@ constexpr int kCols = 32;      // value columns per workgroup
 // beside each chain wave.
 constexpr int kLoaders = 2;
 constexpr int scan_threads(int C) { return 64 * (2 + kLoaders + C / 16); }
+// The grid of a scan over BH heads, nrole workgroups each, heads in groups of
+// eight (one per XCD).  A dimension of a launch holds fewer than 2^32 work
+// items, which workgroups of 512 reach at two million heads, so the grid has
+// rows of at most kRowHeads heads.  (A split scan's many roles only go with
+// few heads.)
+constexpr int kRowHeads = 1 << 18;
+inline dim3 scan_grid(int64_t BH, int nrole) {
+  const int64_t heads = (BH + 7) / 8 * 8;
+  return dim3(static_cast<unsigned>((heads < kRowHeads ? heads : kRowHeads) * nrole),
+              static_cast<unsigned>((heads + kRowHeads - 1) / kRowHeads));
+}
+// the workgroup's head and, of the nrole, its role
+__device__ __forceinline__ int64_t scan_head(int nrole, int* role) {
+  const uint32_t j8 = blockIdx.x >> 3;
+  *role = static_cast<int>(j8 % static_cast<uint32_t>(nrole));
+  return static_cast<int64_t>(blockIdx.y) * kRowHeads + (j8 / static_cast<uint32_t>(nrole)) * 8 + (blockIdx.x & 7);
+}
 struct RunCtx {
   int64_t b, h, bh;
   int v0;        // first value column

@@ -1,6 +1,7 @@
 """Calls of very many heads and few tokens: hundreds of thousands of heads in a
 sequence (a chunk's rows past its end lie beyond 32-bit byte offsets, while
-the valid rows do not).  A head's result does not depend on the others, so the
+the valid rows do not), and millions of sequences (a scan's grid passes 2^32
+work items).  A head's result does not depend on the others, so the
 call must return bit for bit what calls on parts of the heads return."""
 import pytest
 
@@ -57,3 +58,23 @@ def test_rows_past_the_end_with_wide_strides():
         part = step({k: cut(x) for k, x in d.items()}, cut(dO))
         for name, x in part.items():
             assert torch.equal(cut(whole[name]), x), f"{name}, heads {i * n} .. {(i + 1) * n}"
+
+
+def test_scan_grid_past_two_to_the_32():
+    """3000000 sequences of one 64 x 128 head: the state scan's four slabs a
+    head of 384 threads are more work items than one grid dimension takes."""
+    import torch
+    import paper_2604_21100_amd as pdn
+    T, B, parts = 9, 3_000_000, 3
+    assert B * 4 * 384 > 2 ** 32
+    d = _inputs(B, T, 1, 64, 128, "none", 12)
+
+    def forward(x):
+        return pdn.pdn_chunk_fwd(x["q"], x["k"], x["v"], x["beta"], gate="none", precond="identity", chunk=32,
+                                 want_state=False)[0]
+
+    whole = forward(d)
+    n = B // parts
+    for i in range(parts):
+        part = forward({k: x[i * n:(i + 1) * n] for k, x in d.items()})
+        assert torch.equal(whole[i * n:(i + 1) * n], part), f"sequences {i * n} .. {(i + 1) * n}"
