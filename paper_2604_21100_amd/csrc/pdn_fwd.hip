@@ -1609,8 +1609,8 @@ static hipError_t launch_k3(const FwdArgs& a0, hipStream_t s) {
   }
 }
 
-// SAVE: the training forward (k2 in backward mode, k3 also saving the
-// chunk states and E rows)
+// SAVE: the training forward (k2 in backward mode, k3 or the token recurrence
+// also saving the chunk states and E rows)
 template <typename T, int DK, bool SAVE, int C>
 static hipError_t launch_all(const FwdArgs& a, hipStream_t s, hipEvent_t const* ev) {
   hipError_t e;
@@ -1648,21 +1648,25 @@ static hipError_t launch_all(const FwdArgs& a, hipStream_t s, hipEvent_t const* 
       return mark(3);
     }
   }
-  switch (a.gate) {
-    case kGateNone:
-      e = launch_k3<T, DK, kGateNone, SAVE, true, false, C>(a, s); break;
-    case kGateScalar:
-      e = launch_k3<T, DK, kGateScalar, SAVE, true, false, C>(a, s); break;
-    default:
-      e = launch_k3<T, DK, kGateChannel, SAVE, true, false, C>(a, s);
-      break;
+  if (SAVE && step_form(a)) {
+    e = launch_step_tokens(a, sizeof(T) == 2, s);
+  } else {
+    switch (a.gate) {
+      case kGateNone:
+        e = launch_k3<T, DK, kGateNone, SAVE, true, false, C>(a, s); break;
+      case kGateScalar:
+        e = launch_k3<T, DK, kGateScalar, SAVE, true, false, C>(a, s); break;
+      default:
+        e = launch_k3<T, DK, kGateChannel, SAVE, true, false, C>(a, s);
+        break;
+    }
   }
   if (e != hipSuccess) return e;
   return mark(3);
 }
 
-// the backward's forward recompute: k1 (squash), k2 in backward mode and k3
-// saving chunk states and E rows (no output)
+// the backward's forward recompute: k1 (squash), k2 in backward mode and k3 or
+// the token recurrence saving chunk states and E rows (no output)
 template <typename T, int DK, int C>
 static hipError_t launch_recompute(const FwdArgs& a, hipStream_t s, hipEvent_t const* ev) {
   hipError_t e;
@@ -1683,13 +1687,17 @@ static hipError_t launch_recompute(const FwdArgs& a, hipStream_t s, hipEvent_t c
   }
   if (e != hipSuccess) return e;
   if ((e = mark(2)) != hipSuccess) return e;
-  switch (a.gate) {
-    case kGateNone:
-      e = launch_k3<T, DK, kGateNone, true, false, false, C>(a, s); break;
-    case kGateScalar:
-      e = launch_k3<T, DK, kGateScalar, true, false, false, C>(a, s); break;
-    default:
-      e = launch_k3<T, DK, kGateChannel, true, false, false, C>(a, s); break;
+  if (step_form(a)) {
+    e = launch_step_tokens(a, sizeof(T) == 2, s);
+  } else {
+    switch (a.gate) {
+      case kGateNone:
+        e = launch_k3<T, DK, kGateNone, true, false, false, C>(a, s); break;
+      case kGateScalar:
+        e = launch_k3<T, DK, kGateScalar, true, false, false, C>(a, s); break;
+      default:
+        e = launch_k3<T, DK, kGateChannel, true, false, false, C>(a, s); break;
+    }
   }
   if (e != hipSuccess) return e;
   return mark(3);
@@ -1757,22 +1765,15 @@ hipError_t launch_forward(const FwdArgs& a, int io_bf16, hipStream_t s, hipEvent
                        a, nS, nA);
     return hipGetLastError();
   }
-  if (a.T > kStepTokens) {
+  if (train || !step_form(a)) {
     return a.chunk == 32 ? launch_chunks<32>(a, io_bf16, s, ev, train)
                          : launch_chunks<64>(a, io_bf16, s, ev, train);
   }
-  // A few tokens: the token recurrence.  Training forwards run the chunk
-  // kernels for the rows the backward reads and take their outputs from the
-  // recurrence too, so both forwards return the same values.  (The first
-  // three stage events of an inference call mark empty stages.)
+  // a few tokens: the token recurrence alone (the first three stage events
+  // mark empty stages)
   hipError_t e = hipSuccess;
-  if (train) {
-    hipEvent_t e3[4] = {ev ? ev[0] : nullptr, ev ? ev[1] : nullptr, ev ? ev[2] : nullptr, nullptr};
-    e = a.chunk == 32 ? launch_chunks<32>(a, io_bf16, s, e3, true) : launch_chunks<64>(a, io_bf16, s, e3, true);
-  } else {
-    for (int i = 0; ev && i < 3 && e == hipSuccess; ++i)
-      if (ev[i]) e = hipEventRecord(ev[i], s);
-  }
+  for (int i = 0; ev && i < 3 && e == hipSuccess; ++i)
+    if (ev[i]) e = hipEventRecord(ev[i], s);
   if (e == hipSuccess) e = launch_step_tokens(a, io_bf16, s);
   if (e == hipSuccess && ev && ev[3]) e = hipEventRecord(ev[3], s);
   return e;

@@ -174,14 +174,17 @@ hipError_t launch_seg_compose(const FwdArgs& a, bool rev, hipStream_t s);
 // states and E rows for the backward, out forms the output.
 hipError_t launch_fwd_scan_bf16(const FwdArgs& a, bool save, bool out, hipStream_t s);
 
-// The inference forward over at most kStepTokens tokens as the token
-// recurrence (pdn_step.hip): one launch, no workspace.  A token costs it about
+// The forward over at most kStepTokens tokens as the token recurrence
+// (pdn_step.hip): for inference one launch that uses no workspace; training and
+// the backward's recompute launch it in the state scan's place (with Hs set it
+// leaves the rows the backward reads), so every forward returns the same.  A token costs it about
 // 1.3 us of latency (1 to 16 heads; 2.3 us at 256, 8 us at 1024, where the
 // state's arithmetic counts), the chunk kernels take the same time for any T
 // up to a chunk.  d = 128, scalar gate, us at T = 8 and 16: 16 heads 13 and 23
 // against 24, 256 heads 23 and 42 against 41, 1024 heads 70 and 130 against
 // 130; at T = 1, 11 (the host's time), 11 and 23.
 constexpr int kStepTokens = 8;
+inline bool step_form(const FwdArgs& a) { return a.T <= kStepTokens; }
 hipError_t launch_step_tokens(const FwdArgs& a, int io_bf16, hipStream_t s);
 
 struct WsLayout {

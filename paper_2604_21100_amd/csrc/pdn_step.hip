@@ -69,6 +69,19 @@ __global__ __launch_bounds__(256) void step_tokens(FwdArgs a) {
   for (int j = 0; j < R; ++j)
     st[j] = a.S0 ? *reinterpret_cast<const floatx4*>(a.S0 + (bh * DK + r0 + j) * a.dv + v0 + 4 * cg)
                  : floatx4{0.f, 0.f, 0.f, 0.f};
+  // training (one chunk: the calls taken here are shorter): the chunk-start
+  // state and the E rows, which are the tokens' e, the padded ones zero
+  // (saved_idx: bf16 in slabs of 32 columns)
+  constexpr bool SLAB = sizeof(T) == 2;
+  T* er = nullptr;
+  const int64_t se = SLAB ? kStepCols : a.dv;
+  if (a.Hs) {
+    T* hs = static_cast<T*>(a.Hs) + bh * DK * a.dv + (SLAB ? v0 * DK : v0) + 4 * cg;
+#pragma unroll
+    for (int j = 0; j < R; ++j) st4<T>(hs + (r0 + j) * se, st[j][0], st[j][1], st[j][2], st[j][3]);
+    er = static_cast<T*>(a.Er) + bh * a.chunk * a.dv + (SLAB ? v0 * a.chunk : v0) + 4 * cg;
+    for (int r = static_cast<int>(a.T) + (tid >> 3); r < a.chunk; r += 32) st4<T>(er + r * se, 0.f, 0.f, 0.f, 0.f);
+  }
   float A = has_gram(PREC) && a.A0 ? a.A0[bh * DK + c] : 0.f;
   const float mu = PREC == kSquash ? fast_exp(a.log_a_scale[h]) : 0.f;
   for (int64_t t = 0; t < a.T; ++t) {
@@ -149,7 +162,8 @@ __global__ __launch_bounds__(256) void step_tokens(FwdArgs a) {
     }
 #pragma unroll
     for (int j = 0; j < R; ++j) st[j] += sKt[u][r0 + j] * e;
-    if (tid < 8) st4<T>(op, o[0], o[1], o[2], o[3]);
+    if (tid < 8 && a.o) st4<T>(op, o[0], o[1], o[2], o[3]);
+    if (tid >> 3 == 8 && er) st4<T>(er + t * se, e[0], e[1], e[2], e[3]);
     op += HV;
   }
   if (a.S_T)
