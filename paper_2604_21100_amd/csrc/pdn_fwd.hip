@@ -1648,7 +1648,7 @@ static hipError_t launch_all(const FwdArgs& a, hipStream_t s, hipEvent_t const* 
       return mark(3);
     }
   }
-  if (SAVE && step_form(a)) {
+  if (SAVE && step_form(a, sizeof(T) == 2)) {
     e = launch_step_tokens(a, sizeof(T) == 2, s);
   } else {
     switch (a.gate) {
@@ -1687,7 +1687,7 @@ static hipError_t launch_recompute(const FwdArgs& a, hipStream_t s, hipEvent_t c
   }
   if (e != hipSuccess) return e;
   if ((e = mark(2)) != hipSuccess) return e;
-  if (step_form(a)) {
+  if (step_form(a, sizeof(T) == 2)) {
     e = launch_step_tokens(a, sizeof(T) == 2, s);
   } else {
     switch (a.gate) {
@@ -1765,7 +1765,7 @@ hipError_t launch_forward(const FwdArgs& a, int io_bf16, hipStream_t s, hipEvent
                        a, nS, nA);
     return hipGetLastError();
   }
-  if (train || !step_form(a)) {
+  if (train || !step_form(a, io_bf16)) {
     return a.chunk == 32 ? launch_chunks<32>(a, io_bf16, s, ev, train)
                          : launch_chunks<64>(a, io_bf16, s, ev, train);
   }

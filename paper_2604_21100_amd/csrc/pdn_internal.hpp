@@ -177,14 +177,37 @@ hipError_t launch_fwd_scan_bf16(const FwdArgs& a, bool save, bool out, hipStream
 // The forward over at most kStepTokens tokens as the token recurrence
 // (pdn_step.hip): for inference one launch that uses no workspace; training and
 // the backward's recompute launch it in the state scan's place (with Hs set it
-// leaves the rows the backward reads), so every forward returns the same.  A token costs it about
-// 1.3 us of latency (1 to 16 heads; 2.3 us at 256, 8 us at 1024, where the
-// state's arithmetic counts), the chunk kernels take the same time for any T
-// up to a chunk.  d = 128, scalar gate, us at T = 8 and 16: 16 heads 13 and 23
-// against 24, 256 heads 23 and 42 against 41, 1024 heads 70 and 130 against
-// 130; at T = 1, 11 (the host's time), 11 and 23.
+// leaves the rows the backward reads), so every forward returns the same.
+//
+// A token costs it about 1.2 us of latency while its slabs of 32 columns find a
+// compute unit each, and time in proportion to them past about 1024; the chunk
+// kernels take the same time for any T up to a chunk.  Forward with states,
+// us, recurrence at T = 8 against the chunk kernels:
+//   C = 64, d = 128, scalar gate   4 heads 13 / 23   256 23 / 42   1024 71 / 110
+//   fp32, d = 128, C = 64          256 heads 24 / 83   1024 71 / 305
+//   fp32, d = 64, C = 32, no gate, identity          256 13 / 21   1024 34 / 67
+// In bf16 at C = 32 a chunk is little work, and many heads' chunks cost less
+// than eight tokens (T = 8, 6, 4 against the chunk kernels):
+//   64 x 64, identity    64 heads 12 11 11 / 14   256 14 12 11 / 14   1024 35 27 20 / 24
+//   64 x 128, identity   64 heads 12 12 12 / 14   256 21 16 12 / 15   1024 62 47 34 / 35
+//   128 x 128, identity  64 heads 13 12 12 / 14   256 23 18 14 / 20   1024 68 52 38 / 52
+//   64 x 64, squash      64 heads 12 11 11 / 19   256 15 12 11 / 20   1024 36 28 20 / 35
+//   64 x 128, squash     64 heads 13 12 12 / 19   256 21 17 12 / 23   1024 64 48 35 / 46
+//   128 x 128, squash    64 heads 13 11 12 / 18   256 24 19 14 / 28   1024 69 53 39 / 66
+// The lines are the inference forward's; a training step of 7 or 8 tokens pays
+// for the recurrence in one scan step's place up to 3 us of 50 to 80 (256 heads
+// of 64 x 128, squash, C = 32, T = 8: 74 against 70; fp32, 4 heads of 64: 79
+// against 77).
 constexpr int kStepTokens = 8;
-inline bool step_form(const FwdArgs& a) { return a.T <= kStepTokens; }
+inline bool step_form(const FwdArgs& a, bool io_bf16) {
+  int most = kStepTokens;
+  if (io_bf16 && a.chunk == 32) {
+    const int64_t slabs = a.BH * (a.dv / 32);
+    if (!has_gram(a.precond) && slabs > 512) most = a.dk == 64 ? 4 : 6;
+    if (has_gram(a.precond) && a.dk == 64 && slabs > 1024) most = 6;
+  }
+  return a.T <= most;
+}
 hipError_t launch_step_tokens(const FwdArgs& a, int io_bf16, hipStream_t s);
 
 struct WsLayout {

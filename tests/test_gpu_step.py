@@ -85,3 +85,57 @@ def test_pieces_equal_whole(gate):
     torch.cuda.synchronize()
     for x, y in ((torch.cat(parts, 1), whole[0]), (S, whole[1]), (A, whole[2])):
         assert rel_err(x.cpu().numpy(), y.cpu().numpy()) <= 1e-5
+
+
+@pytest.mark.parametrize("precond,gate,dk,dv,H,T,recurrence", [
+    # bf16 at chunk 32: past 512 slabs of 32 columns (1024 with a Gram recurrence) the line falls to 4 or 6 tokens
+    ("identity", "none", 64, 64, 256, 8, True),
+    ("identity", "none", 64, 64, 257, 5, False),
+    ("identity", "none", 64, 64, 257, 4, True),
+    ("external", "scalar", 128, 128, 129, 7, False),
+    ("external", "channel", 128, 128, 129, 6, True),
+    ("squash", "scalar", 64, 128, 256, 8, True),
+    ("squash", "channel", 64, 128, 257, 7, False),
+    ("squash", "none", 64, 128, 257, 6, True),
+    ("squash", "none", 128, 128, 300, 8, True),
+])
+def test_few_tokens_of_many_heads(precond, gate, dk, dv, H, T, recurrence):
+    """Which form takes the call (the recurrence is one launch), and that it
+    returns what the same heads return in calls of few heads."""
+    import ctypes
+    import torch
+    import paper_2604_21100_amd as pdn
+    sq = precond == "squash"
+    spec = pi.small_spec(gate=gate, dk=dk, dv=dv, B=1, H=H, T=T, chunk=32, s0="normal",
+                         a0="lognormal" if sq else "zero")
+    d = to_device(pi.generate(spec, 7300 + H + T), "bf16")
+    if precond == "external":
+        d["ktilde"] = (d["k"].float() * 1.2).to(torch.bfloat16)
+    names = ("g", "beta_p", "g_p", "log_a_scale", "A0", "S0", "ktilde") if sq else ("g", "S0", "ktilde")
+
+    def call(lo, hi, out=None):
+        cut = lambda n: None if d.get(n) is None else (  # noqa: E731  (a copy: aligned)
+            d[n][lo:hi] if n == "log_a_scale" else d[n][:, lo:hi] if n in ("A0", "S0") else d[n][:, :, lo:hi]).clone(memory_format=torch.contiguous_format)
+        main, kw = [cut(n) for n in ("q", "k", "v", "beta")], {n: cut(n) for n in names}
+        kw.update(gate=gate, precond=precond, chunk=32, **(out or {}))
+        return main, kw
+
+    main, kw = call(0, H)
+    whole = pdn.pdn_chunk_fwd(*main, **kw)
+    n = 64
+    for lo in (0, H - n):
+        main, kw = call(lo, lo + n)
+        few = pdn.pdn_chunk_fwd(*main, **kw)   # the recurrence: the oracle's check is above
+        for x, y in ((whole[0][:, :, lo:lo + n], few[0]), (whole[1][:, lo:lo + n], few[1])):
+            e = rel_err(x.float().cpu().numpy(), y.float().cpu().numpy())
+            assert e == 0 if recurrence else e <= tol("bf16")
+    main, kw = call(0, H, dict(zip(("o", "S_T", "A_T"), whole)))
+    prob = pdn.make_problem(1, T, H, dk, dv, gate=gate, precond=precond, chunk=32)
+    kw["workspace"] = torch.empty(pdn.pdn_workspace_size(prob), dtype=torch.uint8, device="cuda")
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        pdn.pdn_chunk_fwd(*main, **kw)
+    nodes = ctypes.c_size_t(0)
+    hip = ctypes.CDLL(pdn.loaded_hip_runtimes()[0])
+    assert hip.hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(nodes)) == 0
+    assert (nodes.value == 1) == recurrence, nodes.value
