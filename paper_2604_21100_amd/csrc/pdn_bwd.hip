@@ -50,14 +50,13 @@ constexpr int BVB = 32;  // value columns per workgroup in the reverse scan
 // true at C = 64.
 
 // A thread's share of a [NR rows] x BVB slab in 16-byte vectors: vector j
-// of thread tid is idx = tid + 256 j (idx < kN), row idx / kSegs
+// of thread tid is idx = tid + 256 j, row idx / kSegs
 template <typename T, int NR>
 struct Slab {
   static constexpr int kVec = 16 / static_cast<int>(sizeof(T));
   static constexpr int kSegs = BVB / kVec;
-  static constexpr int kN = NR * kSegs;
-  static constexpr int kPer = (kN + 255) / 256;
-  static constexpr bool kWhole = kN % 256 == 0;
+  static constexpr int kPer = NR * kSegs / 256;
+  static_assert(NR * kSegs % 256 == 0, "whole vectors a thread (fp32 scan only)");
 };
 
 // sw() for LDS slabs whose rows hold COLS token columns: the XOR stays
@@ -84,7 +83,6 @@ __device__ __forceinline__ void slab_to_rows(T* dst, int64_t ld, const T* src, i
 #pragma unroll
   for (int j = 0; j < SM::kPer; ++j) {
     const int idx = tid + 256 * j;
-    if (!SM::kWhole && idx >= SM::kN) break;
     const int row = idx / SM::kSegs, c0 = (idx % SM::kSegs) * SM::kVec;
     float4 pk;
     T* e = reinterpret_cast<T*>(&pk);
@@ -128,7 +126,6 @@ __device__ __forceinline__ void rev_load_dO(float4 (&d)[NPER], const BwdArgs& ba
 #pragma unroll
   for (int j = 0; j < SM::kPer; ++j) {
     const int idx = x.tid + 256 * j;
-    if (!SM::kWhole && idx >= SM::kN) break;
     const uint32_t row = static_cast<uint32_t>(min(idx / SM::kSegs, last));
     const uint32_t off = (row * static_cast<uint32_t>(HV) + (idx % SM::kSegs) * SM::kVec) * E;
     d[j] = *reinterpret_cast<const float4*>(at_bytes(dob, off));
@@ -202,7 +199,6 @@ __device__ __forceinline__ void rev_stage_dO(const float4 (&v)[Slab<T, C>::kPer]
 #pragma unroll
   for (int j = 0; j < SM::kPer; ++j) {
     const int idx = tid + 256 * j;
-    if (!SM::kWhole && idx >= SM::kN) break;
     const int row = idx / SM::kSegs, c0 = (idx % SM::kSegs) * SM::kVec;
     const float4 raw = pin_here(v[j]);
     const T* e = reinterpret_cast<const T*>(&raw);
@@ -1892,8 +1888,8 @@ BwdWsLayout bwd_ws_layout(int64_t BH, int NT, int dk, int dv, int esz, int gate,
   // the per-channel gate as the decayed ones
   const bool rows = esz == 2, chan = gate == kGateChannel;
   L.Ktr = rows && !chan ? L.f.KtG : take(bh * tp * dk * esz);
-  L.Kw = !chan ? 0 : rows ? L.f.KtG : take(bh * tp * dk * esz);
   if (!rows) {
+    if (chan) L.Kw = take(bh * tp * dk * esz);
     L.QlT = take(bh * nt * dk * C * esz);
     L.KnT = take(bh * nt * dk * C * esz);
   }
@@ -1930,9 +1926,8 @@ static hipError_t launch_bwd_typed(const BwdArgs& ba, hipStream_t s, hipEvent_t 
     if ((e = hipGetLastError()) != hipSuccess) return e;
   } else {
     // split reverse scan: the last segment beside the middle segments'
-    // local runs and transitions, the composed starts, then segments
-    // 0 .. S - 2 (the first pass's middle runs also write dHs, Z and dv rows
-    // for their chunks from the wrong start; the third pass overwrites them)
+    // local runs and transitions (these leave only their end states), the
+    // composed starts, then segments 0 .. S - 2
     const int S = a.seg_cnt;
     BwdArgs b1 = ba;
     b1.f.seg_phase = 1;

@@ -894,15 +894,13 @@ constexpr int BV = 32;  // value columns per workgroup
 
 // One thread's share of a chunk's C x BV value (or output) slab, as 16-byte
 // vectors: vector j of thread tid covers row idx / kSegs, elements
-// [(idx % kSegs) * kVec, + kVec) with idx = tid + 256 j, for idx < kN (at
-// C = 32 in bf16 only the first half of the threads have a vector).
+// [(idx % kSegs) * kVec, + kVec) with idx = tid + 256 j.
 template <typename T, int C>
 struct SlabMap {
   static constexpr int kVec = 16 / static_cast<int>(sizeof(T));
   static constexpr int kSegs = BV / kVec;
-  static constexpr int kN = C * kSegs;
-  static constexpr int kPer = (kN + 255) / 256;
-  static constexpr bool kWhole = kN % 256 == 0;
+  static constexpr int kPer = C * kSegs / 256;
+  static_assert(C * kSegs % 256 == 0, "whole vectors a thread (fp32 scans only)");
 };
 
 // sw() for the [v][t] slabs of C token columns: the XOR keeps the column
@@ -984,7 +982,6 @@ __device__ __forceinline__ void scan_load(ScanFrags<T, DK, GATE, C>& f, const Fw
 #pragma unroll
     for (int j = 0; j < SM::kPer; ++j) {
       const int idx = x.tid + 256 * j;
-      if (!SM::kWhole && idx >= SM::kN) break;
       const uint32_t row = static_cast<uint32_t>(min(idx / SM::kSegs, last));
       const uint32_t off = (row * static_cast<uint32_t>(HV) + (idx % SM::kSegs) * SM::kVec) * E;
       f.v[j] = *reinterpret_cast<const float4*>(at_bytes(vb, off));
@@ -1059,7 +1056,6 @@ __device__ __forceinline__ void stage_values(const float4 (&v)[SlabMap<T, C>::kP
 #pragma unroll
   for (int j = 0; j < SM::kPer; ++j) {
     const int idx = tid + 256 * j;
-    if (!SM::kWhole && idx >= SM::kN) break;
     const int row = idx / SM::kSegs, c0 = (idx % SM::kSegs) * SM::kVec;
     const float4 raw = pin_here(v[j]);
     const T* e = reinterpret_cast<const T*>(&raw);
@@ -1082,7 +1078,6 @@ __device__ __forceinline__ void flush_output(const FwdArgs& a, int i, int n, con
 #pragma unroll
   for (int j = 0; j < SM::kPer; ++j) {
     const int idx = x.tid + 256 * j;
-    if (!SM::kWhole && idx >= SM::kN) break;
     const int row = idx / SM::kSegs, c0 = (idx % SM::kSegs) * SM::kVec;
     float4 pk;
     T* e = reinterpret_cast<T*>(&pk);
@@ -1107,7 +1102,6 @@ __device__ __forceinline__ void flush_slab_t(T* dst, int64_t ld, const T* src, i
 #pragma unroll
   for (int j = 0; j < SM::kPer; ++j) {
     const int idx = tid + 256 * j;
-    if (!SM::kWhole && idx >= SM::kN) break;
     const int row = idx / SM::kSegs, c0 = (idx % SM::kSegs) * SM::kVec;
     float4 pk;
     T* e = reinterpret_cast<T*>(&pk);
@@ -1551,9 +1545,9 @@ WsLayout fwd_ws_layout(int64_t BH, int NT, int dk, int dv, int esz, int gate, in
 template <typename T, int DK, int GATE, int PREC, bool BWD, int C>
 static hipError_t launch_k2(const FwdArgs& a, hipStream_t s) {
   // (without the per-channel gate the bf16 backward reads what the forward scan does)
-  constexpr bool ROWS = sizeof(T) == 2 && GATE != kGateChannel, B = BWD && !ROWS;
+  constexpr bool SHARED = sizeof(T) == 2 && GATE != kGateChannel, B = BWD && !SHARED;
   const dim3 grid(static_cast<unsigned>(a.BH * a.NT));
-  if constexpr (ROWS && PREC != kATQ) {
+  if constexpr (SHARED && PREC != kATQ) {
     if (a.forms_p) {
       hipLaunchKernelGGL((k2_chunk_prep<T, DK, GATE, PREC, B, C, true>), grid, dim3(256), 0, s, a);
       return hipGetLastError();
@@ -1578,11 +1572,9 @@ static hipError_t launch_k2_prec(const FwdArgs& a, hipStream_t s) {
 
 // The state scan: one pass over the chunks, or with a sequence split
 // (scan_split) the three passes: segment 0 next to the middle segments'
-// local scans and transitions, the composition of the segment starts, and
-// segments 1 .. S - 1 from their exact starts.  The first pass's middle
-// segments also write outputs and saved rows for their chunks from the
-// wrong start; the third pass overwrites every one of them.
-// (bf16: pdn_scan.hip)
+// local scans and transitions (these leave only their end states), the
+// composition of the segment starts, and segments 1 .. S - 1 from their exact
+// starts.  (bf16: pdn_scan.hip)
 template <typename T, int DK, int GATE, bool SAVE, bool OUT, bool LA, int C>
 static hipError_t launch_k3(const FwdArgs& a0, hipStream_t s) {
   if constexpr (sizeof(T) == 2) {

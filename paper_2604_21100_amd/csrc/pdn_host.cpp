@@ -218,7 +218,7 @@ static void set_forward_ws(pdn::FwdArgs& a, const pdn::WsLayout& L, const pdn_pr
   }
   if (p->io == PDN_BF16) {
     a.Kd = w + L.KtG;
-    a.forms_p = pdn::scan_forms_p(a.BH, a.NT, a.dv, a.gate, a.precond, L.split);
+    a.forms_p = pdn::scan_forms_p(a.BH, a.NT, a.dv, a.gate, a.precond);
   }
   else a.KtG = w + L.KtG;
   a.Tm = w + L.Tm;
@@ -235,8 +235,9 @@ static void set_forward_ws(pdn::FwdArgs& a, const pdn::WsLayout& L, const pdn_pr
 
 static void set_residuals(pdn::FwdArgs& f, const pdn::BwdWsLayout& L, char* w) {
   f.Hs = w + L.Hs; f.Er = w + L.Er;
-  f.Ktr = w + L.Ktr; f.Kw = f.gate == pdn::kGateChannel ? w + L.Kw : nullptr;
+  f.Ktr = w + L.Ktr;
   if (!f.Kd) {   // fp32
+    if (f.gate == pdn::kGateChannel) f.Kw = w + L.Kw;
     f.PtT = w + L.PtT; f.MtT = w + L.MtT; f.QlT = w + L.QlT; f.KnT = w + L.KnT;
   }
 }

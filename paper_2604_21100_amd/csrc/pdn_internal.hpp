@@ -73,7 +73,7 @@ struct FwdArgs {
   void* PtT;      // [BH, NT, C, C] io    P^T
   void* MtT;      // [BH, NT, C, C] io    M^T, M = (I + At)^{-1} (T = M Diag(beta))
   void* Ktr;      // [BH, Tpad, dk] io    write key rows (bf16 without the per-channel gate: Kd)
-  void* Kw;       // [BH, Tpad, dk] io    w_r o write key rows (per-channel gate, bf16: Kd; else NULL)
+  void* Kw;       // [BH, Tpad, dk] io    w_r o write key rows (fp32 with the per-channel gate only; bf16: Kd)
   void* QlT;      // [BH, NT, dk, C] io   (Diag(lam) Q)^T per chunk
   void* KnT;      // [BH, NT, dk, C] io   -(Diag(lam) K)^T per chunk
   // sequence split of the state scan (see scan_split): seg_phase 0 = one
@@ -128,9 +128,10 @@ inline ScanSplit scan_split(int64_t BH, int NT, int dk, int dv) {
 // tokens 206 / 240; 64 of 777 57 / 55; 16 of 32768 (split, 192 workgroups) a
 // scan pass 327 / 269, two of them against 50 saved in the preparation.
 // (The per-channel gate's P has its decay inside the contraction, and linear
-// attention's preparation rewrites the queries anyway.)
-inline bool scan_forms_p(int64_t BH, int NT, int dv, int gate, int precond, const ScanSplit& sp) {
-  return gate != kGateChannel && precond != kATQ && sp.S < 3 && BH * (dv / 32) >= kScanCUs && NT >= 32;
+// attention's preparation rewrites the queries anyway.  A scan of as many
+// slabs as compute units is never split: scan_split's first pass holds them all.)
+inline bool scan_forms_p(int64_t BH, int NT, int dv, int gate, int precond) {
+  return gate != kGateChannel && precond != kATQ && BH * (dv / 32) >= kScanCUs && NT >= 32;
 }
 
 // Backward-only arguments and workspace (the forward recompute uses f).

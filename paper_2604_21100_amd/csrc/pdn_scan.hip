@@ -662,31 +662,35 @@ __global__ __launch_bounds__(scan_threads(C), 2) void fwd_scan(FwdArgs a) {
   x.v0 = x.probe ? 0 : slab * kCols;
   const int pv0 = x.probe ? (slab - nslab) * kCols : 0;
   // middle segments of the first pass need only their end states
-  if (a.seg_phase == 1 && seg > 0) fwd_run<DK, GATE, false, false, LA, C, PSCAN>(a, x, seg, pv0, sm);
-  else fwd_run<DK, GATE, SAVE, OUT, LA, C, PSCAN>(a, x, seg, pv0, sm);
+  if constexpr (!PSCAN) {
+    if (a.seg_phase == 1 && seg > 0) {
+      fwd_run<DK, GATE, false, false, LA, C, false>(a, x, seg, pv0, sm);
+      return;
+    }
+  }
+  fwd_run<DK, GATE, SAVE, OUT, LA, C, PSCAN>(a, x, seg, pv0, sm);
 }
 
 template <int DK, int GATE, bool SAVE, bool OUT, bool LA, int C, bool PSCAN>
 hipError_t launch_typed(const FwdArgs& a0, hipStream_t s) {
   FwdArgs a = a0;
-  const int nslab = a.dv / kCols, npslab = DK / kCols;
-  if (a.seg_cnt < 3) {
-    a.seg_phase = 0;
-    hipLaunchKernelGGL((fwd_scan<DK, GATE, SAVE, OUT, LA, C, PSCAN>), scan_grid(a.BH, nslab), dim3(scan_threads(C)),
-                       0, s, a);
+  const int nslab = a.dv / kCols;
+  const auto launch = [&](int phase, int nrole) {
+    a.seg_phase = phase;
+    hipLaunchKernelGGL((fwd_scan<DK, GATE, SAVE, OUT, LA, C, PSCAN>), scan_grid(a.BH, nrole), dim3(scan_threads(C)), 0,
+                       s, a);
     return hipGetLastError();
+  };
+  if (a.seg_cnt < 3) return launch(0, nslab);
+  if constexpr (PSCAN) {
+    return hipErrorInvalidValue;   // (scan_forms_p: never a split scan)
+  } else {
+    const int S = a.seg_cnt;
+    hipError_t e = launch(1, nslab + (S - 2) * (nslab + DK / kCols));
+    if (e != hipSuccess) return e;
+    if ((e = launch_seg_compose(a, false, s)) != hipSuccess) return e;
+    return launch(3, (S - 1) * nslab);
   }
-  const int S = a.seg_cnt;
-  a.seg_phase = 1;
-  hipLaunchKernelGGL((fwd_scan<DK, GATE, SAVE, OUT, LA, C, PSCAN>),
-                     scan_grid(a.BH, nslab + (S - 2) * (nslab + npslab)), dim3(scan_threads(C)), 0, s, a);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  if ((e = launch_seg_compose(a, false, s)) != hipSuccess) return e;
-  a.seg_phase = 3;
-  hipLaunchKernelGGL((fwd_scan<DK, GATE, SAVE, OUT, LA, C, PSCAN>), scan_grid(a.BH, (S - 1) * nslab),
-                     dim3(scan_threads(C)), 0, s, a);
-  return hipGetLastError();
 }
 
 template <int DK, int GATE, int C, bool PSCAN>
