@@ -183,7 +183,9 @@ typedef struct {
 } pdn_bwd_out;
 
 /* Bytes of workspace pdn_chunk_fwd (with_bwd = 0) or pdn_chunk_bwd
- * (with_bwd = 1) needs for this problem.  Host-only, no HIP call.
+ * (with_bwd = 1) needs for this problem.  Host-only, no HIP call.  (A forward
+ * of up to eight tokens may run as the token recurrence, which uses none of
+ * it; the size is the same, and so is every check of it.)
  * Returns PDN_ERR_NULL / SHAPE / DTYPE / UNSUPPORTED / VALUE for a bad
  * problem; *bytes is written only on PDN_OK. */
 pdn_status pdn_workspace_size(const pdn_problem* problem, int with_bwd,
@@ -245,10 +247,14 @@ size_t pdn_noalloc_scratch_bytes(void);
  * handles passed as void*) on `hip_stream` at the stage boundaries, for
  * timing individual kernels:
  *   stage_events[0]  before the preconditioner scan (k1_*; empty unless
- *                    SQUASH)
+ *                    SQUASH, DIAG_SM or ATQ)
  *   stage_events[1]  after it / before the per-chunk prep kernel (k2)
  *   stage_events[2]  after k2 / before the inter-chunk scan + output (k3)
  *   stage_events[3]  after k3
+ * (k3: the state scan of either io type.)  A forward of up to eight tokens may
+ * run as the token recurrence, one launch between [2] and [3]: the stages
+ * before it are then empty, or in pdn_chunk_fwd_train as above with the
+ * recurrence in k3's place.
  * n_events must be 4 (else PDN_ERR_VALUE); a NULL entry is not recorded
  * (each record costs a few microseconds of GPU time between kernels, so a
  * caller timing one stage passes only its two boundaries).  The events stay
@@ -274,7 +280,7 @@ pdn_status pdn_chunk_bwd(const pdn_problem* problem, const pdn_inputs* in,
  * at its stage boundaries (n_events must be PDN_BWD_STAGE_EVENTS):
  *   [0] start  [1] after the preconditioner recompute (k1_*)
  *   [2] after the per-chunk prep recompute (k2, backward mode)
- *   [3] after the state-saving forward scan (k3)
+ *   [3] after the state-saving forward scan (k3, or the token recurrence)
  *   [4] after the reverse state-adjoint scan (r1)
  *   [5] after the per-chunk adjoints and gradients (p12)
  *   [6] after the preconditioner's reverse scan (pc_*) or the key combine

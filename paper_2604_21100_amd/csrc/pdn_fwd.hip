@@ -195,7 +195,8 @@ struct K2Smem {
 // What bounds it: a block's chain of phases (loads, two walks of the
 // preconditioner, the C x C product, the solve), overlapped by the blocks that
 // share a CU.  1B layer (B = 4, T = 4096, H = 16, d = 128, scalar gate): 101 us
-// with three blocks per CU, the queries read and P written; 81 us with PSCAN.
+// with three blocks per CU, the queries read and P written; 79 us with PSCAN
+// (176 MB by the counters, 2.2 TB/s).
 // Of the 101, timing copies put 15 in the solve, 26 in the stores, 8 in the
 // squash and 8 in the MFMA.
 template <typename T, int DK, int GATE, int PREC, bool BWD, int C, bool PSCAN>

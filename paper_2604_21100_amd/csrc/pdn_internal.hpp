@@ -99,6 +99,15 @@ struct FwdArgs {
 // steps to about 2 NT / S; S is the largest count whose first pass still
 // fits one workgroup per compute unit of the target device, with at least
 // kSegMinChunks chunks per segment.
+//
+// kSegMinChunks was set for scans of 2.5 to 3 us a step and still fits the fp32
+// ones; a bf16 step now takes 1.0 to 1.6 us while the split costs two more
+// launches and a composition of 5 to 7 us, so short bf16 runs would be faster
+// unsplit.  Forward, us, split against unsplit at 12, 32 and 64 chunks (d = 128,
+// scalar gate):
+//   C = 64   1 head 43 : 35  70 : 53  123 : 83    8 heads 46 : 36  63 : 56  78 : 88    16 heads 49 : 38  65 : 60  98 : 102
+//   C = 32   1 head 35 : 27  58 : 37  105 : 57    8 heads 36 : 28  49 : 39  60 : 61    16 heads 38 : 27  48 : 42  64 : 64
+// (S, and with it the workspace, goes by the problem's sizes alone.)
 constexpr int kScanCUs = 256;       // compute units of MI355X
 constexpr int kSegMinChunks = 4;
 constexpr int kSegMax = 16;
@@ -121,12 +130,21 @@ inline ScanSplit scan_split(int64_t BH, int NT, int dk, int dv) {
 
 // Whether the bf16 state scan forms P itself from the query rows and write
 // keys it holds, rather than the chunk preparation writing it (which then must
-// read the queries): 100 to 133 MB less traffic at the 1B layer, for 40 more
-// MFMA and 48 KB more LDS reads a step in the scan.  Worth it where the scan
-// waits for memory: its slabs fill the chip and its runs are long.  Forward
-// passes, d = 128, scalar gate, formed against written, us: 64 heads of 4096
-// tokens 206 / 240; 64 of 777 57 / 55; 16 of 32768 (split, 192 workgroups) a
-// scan pass 327 / 269, two of them against 50 saved in the preparation.
+// read the queries): 100 to 133 MB less traffic at the 1B layer, for 48 more
+// MFMA and 48 KB more LDS reads a chunk in each of a head's scan workgroups
+// (C = 64, d = 128).  Worth it where that traffic leaves the last-level cache
+// (256 MB): many heads and long runs.  Forward / training step, us, P written
+// against formed, at 16, 32 and 64 chunks:
+//   C = 64, 64 heads of 128, scalar gate  61 : 61 / 210 : 204   97 : 100 / 411 : 408   231 : 199 / 764 : 753
+//   C = 64, 64 heads of 128, no gate      60 : 55 / 202 : 194   95 :  92 / 399 : 396   225 : 192 / 748 : 739
+//   C = 64, 64 heads of 64 x 128, scalar  47 : 49 / 139 : 139   76 :  77 / 281 : 288   162 : 144 / 540 : 537
+//   C = 64, 128 heads of 64, scalar       68 : 63 / 201 : 202  119 : 106 / 397 : 390   266 : 224 / 741 : 727
+//   C = 32, 64 heads of 128, scalar       36 : 39 / 124 : 128   54 :  58 / 239 : 245    89 :  94 / 457 : 458
+//   C = 32, 128 heads of 128, scalar      57 : 60 / 242 : 245   91 :  96 / 465 : 462   191 : 182 / 849 : 841
+//   C = 32, 256 heads of 64, scalar       56 : 55 / 203 : 201   93 :  92 / 389 : 383   212 : 192 / 716 : 708
+// So the line is too low by up to 8 % for a forward of 64 heads in chunks of 32
+// (the present scans with P formed are still 1.5 times as fast there as the ones
+// it came with), and too high by up to 10 % for heads of 64 in chunks of 64.
 // (The per-channel gate's P has its decay inside the contraction, and linear
 // attention's preparation rewrites the queries anyway.  A scan of as many
 // slabs as compute units is never split: scan_split's first pass holds them all.)

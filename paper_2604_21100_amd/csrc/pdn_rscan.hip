@@ -18,10 +18,12 @@
 // reads them transposed from memory needs P^T, M^T and both decayed
 // transposes written for it: 200 MB more in the case below.)
 //
-// What bounds it (B = 4, T = 4096, H = 16, d = 128, scalar gate): HBM, about
-// 680 MB in 180 us (225 with the rows of a chunk split over four waves);
-// k2 in the same step went from 146 to 106 us.  On 16 heads of 32768 tokens,
-// first pass, 500 -> 340 us.
+// What bounds it (B = 4, T = 4096, H = 16, d = 128, scalar gate): a step's
+// memory side, 608 MB by the counters in 170 us, 3.6 TB/s of the 5.1 a large
+// copy reaches (225 us with the rows of a chunk split over four waves); k2,
+// which writes no transposes for it, went from 146 to 106 us in the same step
+// (79 since the forward scan forms P).  On 16 heads of 32768 tokens, first pass,
+// 500 -> 320 us.
 #include "pdn_tile.hpp"
 
 namespace pdn {

@@ -18,15 +18,16 @@
 // leaves in LDS.
 //
 // What bounds it (one launch at B = 4, T = 4096, H = 16, d = 128, scalar gate,
-// C = 64; 256 workgroups of 64 steps): HBM.  It reads q, k, v, the write keys,
-// M and P once (the four workgroups of a head share an XCD's L2) and writes
-// o, 480 MB by the counters in 122 us, 3.9 TB/s of the 5.1 a large copy
-// reaches; keeping the backward's rows too, 680 MB in 183 us.  With one role
-// running alone a step takes 1.0 us (chain: 38 MFMA in a row of dependent
-// products), 1.0 us (loads) and 1.1 us (output), 1.9 us together.  The form
-// before this one, a chunk's rows split over four waves with three exchanges
-// through LDS a step, took 163 us (240 keeping rows).  On 16 heads of 32768
-// tokens (192 workgroups of 171 steps in the first pass) 374 -> 269 us.
+// C = 64; 256 workgroups of 64 steps, P formed here): a step's memory side.  It
+// reads q, k, v, the write keys and M once (the four workgroups of a head share
+// an XCD's L2) and writes o, 374 MB by the counters in 111 us, 3.4 TB/s of the
+// 5.1 a large copy reaches; keeping the backward's rows too, 600 MB in 181 us,
+// 3.3 TB/s.  With P read instead of formed, 122 us: a step 1.9 us, and with one
+// role running alone 1.0 us (chain: 38 MFMA in a row of dependent products),
+// 1.0 us (loads) and 1.1 us (output).  The form before this one, a chunk's rows
+// split over four waves with three exchanges through LDS a step, took 163 us
+// (240 keeping rows).  On 16 heads of 32768 tokens (192 workgroups of 171 steps
+// in the first pass, P read) 374 -> 269 us.
 #include "pdn_tile.hpp"
 
 namespace pdn {
