@@ -174,13 +174,13 @@ constexpr int kBufWord3 = 0x00020000;
 // valid row, so accesses to the rows past it are dropped by the range check.
 // Their offsets must then not wrap: with hundreds of thousands of heads
 // (a row stride of H d elements) r * stride passes 2^32 while the valid rows'
-// offsets still fit, and a wrapped one would fall on another row.  Such an
-// offset becomes kPastRange, past every range (512 bytes short of 2^32, so
-// that a column offset added to it does not wrap either).
+// offsets still fit, and a wrapped one would fall on another row.  A row that
+// no chunk has therefore takes kPastRange, past every range (512 bytes short of
+// 2^32, so that a column offset added to it does not wrap either).
 constexpr uint32_t kPastRange = 0xfffffe00u;
-__device__ __forceinline__ uint32_t row_off(uint32_t r, uint32_t stride, uint32_t x) {
-  const uint64_t o = static_cast<uint64_t>(r) * stride + x;
-  return o < kPastRange ? static_cast<uint32_t>(o) : kPastRange;
+// offset of row r, x bytes in; rows: the tokens a chunk has at most
+__device__ __forceinline__ uint32_t row_off(int r, uint32_t stride, uint32_t x, int rows) {
+  return r < rows ? static_cast<uint32_t>(r) * stride + x : kPastRange;
 }
 
 constexpr float kLn2 = 0.6931471805599453f;

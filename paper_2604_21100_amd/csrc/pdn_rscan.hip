@@ -252,19 +252,20 @@ struct RevLoader {
     g = CH ? at(a.G, ci * (DK * 4)) : nullptr;
     hd = static_cast<uint32_t>(a.H * DK * 2);
     hv = static_cast<uint32_t>(a.H * a.dv * 2);
+    const int nrow = static_cast<int>(min<int64_t>(C, a.T));
     heads = a.BH;
     tok1 = tok2 = a.T - t0;
     n1 = n2 = x.c1 - x.c0;
     probe = x.probe;
 #pragma unroll
     for (int j = 0; j < NK; ++j) {
-      vk[j] = unit_src<DK / 8>(lw * NK + j, l, CH ? DK * 2 : hd);
+      vk[j] = unit_src<DK / 8>(lw * NK + j, l, CH ? DK * 2 : hd, CH ? C : nrow);
       vt[j] = unit_src<DK / 8>(lw * NK + j, l, DK * 2);
     }
 #pragma unroll
     for (int j = 0; j < NM; ++j) vm[j] = unit_src<C / 8>(lw * NM + j, l, C * 2);
 #pragma unroll
-    for (int j = 0; j < NV; ++j) vv[j] = unit_src<kCols / 8>(lw * NV + j, l, hv);
+    for (int j = 0; j < NV; ++j) vv[j] = unit_src<kCols / 8>(lw * NV + j, l, hv, nrow);
     vg = 16 * l;
   }
   // (past the run: empty ranges, no traffic; rows past the sequence end are
@@ -380,7 +381,7 @@ __device__ __forceinline__ void rev_run(const BwdArgs& ba, const RunCtx& x, int 
     char* zr = static_cast<char*>(ba.Zr) + (ci * C * a.dv + x.v0 * C) * 2;
     char* dv = static_cast<char*>(ba.dv) + (((x.b * a.T + top * C) * a.H + x.h) * a.dv + x.v0) * 2;
     const uint32_t hv = static_cast<uint32_t>(a.H * a.dv * 2);
-    const uint32_t os = (r0 * kCols + 8 * g) * 2, ox = row_off(32 * f0 + r0, hv, 16 * g);
+    const uint32_t os = (r0 * kCols + 8 * g) * 2, ox = row_off(32 * f0 + r0, hv, 16 * g, static_cast<int>(min<int64_t>(C, a.T)));
     int64_t left = a.T - top * C;
     lds_sync();
     for (int j = 0; j < cnt; ++j) {

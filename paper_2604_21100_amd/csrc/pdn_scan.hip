@@ -256,15 +256,16 @@ struct FwdLoader {
 
   __device__ __forceinline__ FwdLoader(const FwdArgs& a, int lw, int l) {
     const uint32_t hd = static_cast<uint32_t>(a.H) * DK * 2u, hv = static_cast<uint32_t>(a.H) * a.dv * 2u;
+    const int nrow = static_cast<int>(min<int64_t>(C, a.T));
 #pragma unroll
     for (int j = 0; j < NK; ++j) {
-      if (!LA) vk[j] = unit_src<DK / 8>(lw * NK + j, l, CH ? DK * 2u : hd);
+      if (!LA) vk[j] = unit_src<DK / 8>(lw * NK + j, l, CH ? DK * 2u : hd, CH ? C : nrow);
       vt[j] = unit_src<DK / 8>(lw * NK + j, l, DK * 2u);
     }
 #pragma unroll
     for (int j = 0; j < NM; ++j) vm[j] = unit_src<C / 8>(lw * NM + j, l, C * 2u);
 #pragma unroll
-    for (int j = 0; j < NV; ++j) vv[j] = unit_src<kCols / 8>(lw * NV + j, l, hv);
+    for (int j = 0; j < NV; ++j) vv[j] = unit_src<kCols / 8>(lw * NV + j, l, hv, nrow);
     vg = 16u * l;
   }
   // the next chunk into the stage at sg (past the run: empty ranges, no
@@ -334,15 +335,15 @@ struct OutLanes {
   static constexpr bool WS = GATE == kGateChannel || LA;
   uint32_t q, q1, p, g, o;   // q, q1: the pair's two query rows
   bool odd;
-  __device__ __forceinline__ OutLanes(const ChunkCursor& c, int ow, int l) {
+  __device__ __forceinline__ OutLanes(const ChunkCursor& c, int ow, int l, int rows) {
     const int m = l & 15, lg = l >> 4, r = 16 * ow + m;
     odd = m & 1;
     const uint32_t qrow = WS ? DK * 2 : c.hd, qc = 64 * (m & 1) + 16 * lg;
-    q = row_off(r & ~1, qrow, qc);
-    q1 = row_off(r | 1, qrow, qc);
+    q = row_off(r & ~1, qrow, qc, WS ? C : rows);
+    q1 = row_off(r | 1, qrow, qc, WS ? C : rows);
     p = C == 64 ? (r & ~1) * (C * 2) + 64 * (m & 1) + 16 * lg : r * (C * 2) + 16 * lg;
     g = (12 + r / (C / 4)) * (2 * C) + C + (r % (C / 4)) * 4;   // G_r, among the scalars in M
-    o = row_off(r, c.hv, 16 * lg);
+    o = row_off(r, c.hv, 16 * lg, rows);
   }
 };
 
@@ -547,7 +548,7 @@ __device__ __forceinline__ void fwd_run(const FwdArgs& a, const RunCtx& x, int s
     const int ow = w < 4 ? w - 2 : w - 4;
     ChunkCursor c;
     c.start<DK, GATE, C, LA>(a, x);
-    const OutLanes<DK, GATE, C, LA> lanes(c, ow, l);
+    const OutLanes<DK, GATE, C, LA> lanes(c, ow, l, static_cast<int>(min<int64_t>(C, a.T)));
     char* ob = static_cast<char*>(a.o) + ((x.b * a.T + static_cast<int64_t>(x.c0) * C) * a.H + x.h) * a.dv * 2 + x.v0 * 2;
     int64_t left = c.tokens;
     constexpr bool ROWS = OUT || (SAVE && PSCAN);   // the query rows are needed

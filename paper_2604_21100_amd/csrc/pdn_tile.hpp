@@ -111,7 +111,8 @@ inline dim3 scan_grid(int64_t BH, int nrole) {
 __device__ __forceinline__ int64_t scan_head(int nrole, int* role) {
   const uint32_t j8 = blockIdx.x >> 3;
   *role = static_cast<int>(j8 % static_cast<uint32_t>(nrole));
-  return static_cast<int64_t>(blockIdx.y) * kRowHeads + (j8 / static_cast<uint32_t>(nrole)) * 8 + (blockIdx.x & 7);
+  // (BH is below 2^31, so this fits 32 bits, and said so the divisions by H are short)
+  return static_cast<uint32_t>(blockIdx.y * kRowHeads + (j8 / static_cast<uint32_t>(nrole)) * 8 + (blockIdx.x & 7));
 }
 struct RunCtx {
   int64_t b, h, bh;
@@ -133,12 +134,13 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_rsrc(const char* base, uin
 
 // Memory to LDS, 1 KB (64 lanes of 16 bytes) an instruction: unit u of a tile
 // of NCH chunks a row is its 64 / NCH rows from u * 64 / NCH.  The XOR order
-// of the tile is in the lanes' source offsets.
+// of the tile is in the lanes' source offsets.  rows: see row_off (workspace
+// rows, which no stride separates, need no limit).
 template <int NCH>
-__device__ __forceinline__ uint32_t unit_src(int u, int l, uint32_t row_bytes) {
+__device__ __forceinline__ uint32_t unit_src(int u, int l, uint32_t row_bytes, int rows = 1 << 30) {
   const int r = u * (64 / NCH) + l / NCH;
   const int ch = (tile_off<NCH>(r, l % NCH) / 16) % NCH;   // the chunk at position l % NCH of its row
-  return row_off(static_cast<uint32_t>(r), row_bytes, 16u * ch);
+  return row_off(r, row_bytes, 16u * ch, rows);
 }
 __device__ __forceinline__ void unit_copy(__amdgpu_buffer_rsrc_t r, uint32_t off, lds_char* dst) {
   __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)dst, 16, static_cast<int>(off),
